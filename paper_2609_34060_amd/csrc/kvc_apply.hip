@@ -17,7 +17,8 @@
 // since one counter covers loads and stores); the tiles of a wave are software-pipelined in pairs, the loads of the
 // next tile in flight while this tile is corrected and stored.
 //
-// float32 caches: a VALU kernel with the basis in LDS (float32 throughout, for the 1e-5 storage tolerance).
+// float32 caches: the same contraction on the fp32 matrix instruction (float32 throughout, for the 1e-5 storage
+// tolerance).
 #include "kvc_device.h"
 #include "kvc_launch.h"
 
@@ -25,12 +26,9 @@ namespace kvc {
 
 constexpr int kApplyWaves = 4;
 constexpr int kApplyThreads = kApplyWaves * kWave;
-constexpr int kApplyTilesPerWave = 8;                                   // float32 kernel
-constexpr int kApplyChunk = kApplyWaves * kApplyTilesPerWave * 16;      // tokens per workgroup (float32 kernel)
+constexpr int kApplyF32Tiles = 4;                                       // float32 kernel: 16-token tiles per wave
 constexpr int kApplyChunkTokens = 256;                                  // bf16 kernel: tokens per workgroup
 constexpr int kApplyRopeChunkTokens = 1024;                             // the same with rotary keys
-
-int apply_chunk_tokens() { return kApplyChunk; }
 
 // LDS of the bf16 kernel: basis hi/lo [D][KP] each, then the block-table slices of the workgroup's token chunk for
 // the source and the destination sequence (nblk entries each: a chunk of c tokens spans at most c / bs + 1 blocks).
@@ -262,12 +260,19 @@ __global__ __launch_bounds__(W * kWave) void apply_bf16_mfma(ApplyArgs a, int tp
   }
 }
 
-// float32 caches: each thread owns 4 features of one token; the rank loop runs over B in LDS.
-template <int D>
-__global__ __launch_bounds__(kApplyThreads) void apply_f32_valu(ApplyArgs a) {
-  extern __shared__ __attribute__((aligned(16))) float s_b[];  // [r][D]
-  constexpr int LPT = D / 4;                                   // lanes per token
-  constexpr int TPP = kApplyThreads / LPT;                     // tokens per pass
+// float32 caches, on v_mfma_f32_16x16x4_f32 (fp32 products and sums): D^T = B^T A^T + C^T as above, M = feature, N =
+// token, K = rank.  Lane (g, n) holds the features 16 mt + 4 g .. + 3 of token n (16-byte row loads and stores, the
+// accumulator starts from them) and the coefficients of ranks 16 q + 4 g .. + 3; step (q, e) multiplies element e, with
+// B^T read from LDS in the same order (rows padded by 4 ranks: the 16 lanes of a read cover all banks).  A workgroup of
+// four waves stages the basis and the table slices once for 64 tpw tokens; the next tile's loads are in flight while
+// this one is finished.  Latency-bound at a few hundred tokens (2 layers x 4 heads x 64, 256 tokens, rank 8:
+// APPLY_NEW us against 15.7 us for one FMA chain per feature with a dependent table, coefficient and row load per token),
+// memory-bound from a few thousand on.
+template <int D, int KQ>
+__global__ __launch_bounds__(kApplyThreads) void apply_f32_mfma(ApplyArgs a, int tpw, int nblk) {
+  constexpr int MT = D / 16, KP = 16 * KQ, LDB = KP + 4;
+  extern __shared__ __attribute__((aligned(16))) float s_b[];  // B^T [D][LDB], then the table slices [2][nblk]
+  int32_t* s_tab = reinterpret_cast<int32_t*>(s_b + D * LDB);
 
   const int nl = a.num_layers;
   const int il = grid_item_layer(a.chunk_order);
@@ -280,13 +285,14 @@ __global__ __launch_bounds__(kApplyThreads) void apply_f32_valu(ApplyArgs a) {
 
   const kvc_item* itp = a.items + item_id;
   const int T = itp->num_tokens;
-  const int t_begin = grid_chunk(a.chunk_order) * kApplyChunk;
-  if (t_begin >= T) return;
+  const int chunk = kApplyWaves * 16 * tpw;
+  const int t_begin = grid_chunk(a.chunk_order) * chunk;
+  if (t_begin >= T) return;  // whole workgroup
+  const int t_end = min(T, t_begin + chunk);
   const int r = itp->state.rank;
   const int Tdecl = itp->state.num_tokens;
   const int Ts = r > 0 ? min(Tdecl, T) : 0;
-  const int32_t* src_tab = a.src_tables ? a.src_tables + (int64_t)item_id * a.max_blocks : nullptr;
-  const int32_t* dst_tab = a.dst_tables ? a.dst_tables + (int64_t)item_id * a.max_blocks : nullptr;
+  const int src_off = itp->src_offset, dst_off = itp->dst_offset;
   const bool per_layer = itp->state.grouping == KVC_GROUP_LAYER;
   const int64_t unit = per_layer ? (int64_t)layer * 2 + kv : unit_index(layer, kv, head, H);
   const int bstride = per_layer ? H * D : D;
@@ -294,6 +300,19 @@ __global__ __launch_bounds__(kApplyThreads) void apply_f32_valu(ApplyArgs a) {
   const float* basis = itp->state.basis + unit * (int64_t)r * bstride + (per_layer ? head * D : 0);
   const float* src_pool = static_cast<const float*>(kv ? a.layers.v[lrel] : a.layers.k[lrel]);
   float* dst_pool = static_cast<float*>(const_cast<void*>(kv ? a.layers.v[lrel] : a.layers.k[lrel]));
+  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane >> 4, n = lane & 15;
+  const bool correct = t_begin < Ts;  // uniform over the workgroup
+
+  const int bs = a.pv.block_size, bsh = a.pv.block_shift;
+  auto lblock = [&](int p) { return bsh >= 0 ? p >> bsh : p / bs; };
+  const int lb0s = lblock(src_off + t_begin), lb0d = lblock(dst_off + t_begin);
+  {
+    const int ns = lblock(src_off + t_end - 1) - lb0s + 1, nd = lblock(dst_off + t_end - 1) - lb0d + 1;
+    const int32_t* st = a.src_tables ? a.src_tables + (int64_t)item_id * a.max_blocks : nullptr;
+    const int32_t* dt = a.dst_tables ? a.dst_tables + (int64_t)item_id * a.max_blocks : nullptr;
+    for (int i = tid; i < ns; i += kApplyThreads) s_tab[i] = st ? st[lb0s + i] : lb0s + i;
+    for (int i = tid; i < nd; i += kApplyThreads) s_tab[nblk + i] = dt ? dt[lb0d + i] : lb0d + i;
+  }
 
   // keys of a rotary cache: C_dst = R(pd - ps) C_src + A (B R(pd)^T), with the angle tables in LDS
   __shared__ float s_rope[4][D / 2];
@@ -307,51 +326,116 @@ __global__ __launch_bounds__(kApplyThreads) void apply_f32_valu(ApplyArgs a) {
     rope_table(a.pv.rope, D, (double)pd, s_rope[2], s_rope[3]);
     __syncthreads();
   }
-  const bool correct = t_begin < Ts;
   if (correct) {
-    for (int e = threadIdx.x; e < r * D; e += kApplyThreads) {
-      const int k = e / D, f = e - k * D;
-      float x = basis[k * bstride + f];
-      if (rope) {
-        const int i = rope_pair(style, D, f);
-        x = rope_rotated(rope_first(style, D, f), x, basis[k * bstride + rope_partner(style, D, f)], s_rope[2][i],
-                         s_rope[3][i]);
-      }
-      s_b[e] = x;
-    }
-    __syncthreads();
-  }
-  const int sub = threadIdx.x / LPT;
-  const int f0 = 4 * (threadIdx.x % LPT);
-  const int t_end = min(T, t_begin + kApplyChunk);
-  for (int t = t_begin + sub; t < t_end; t += TPP) {
-    const int64_t so = row_offset(a.pv, src_tab, itp->src_offset, t, head);
-    const int64_t dof = row_offset(a.pv, dst_tab, itp->dst_offset, t, head);
-    if (so < 0 || dof < 0) continue;
-    const f32x4 s = *reinterpret_cast<const f32x4*>(src_pool + so + f0);
-    f32x4 o = s;
-    if (shift) {  // the source rotated by pd - ps (the four features' partners: another quad, or inside this one)
-      const int pf = rope_partner(style, D, f0) & ~3;
-      const f32x4 y = *reinterpret_cast<const f32x4*>(src_pool + so + pf);
+    for (int e = tid; e < D * (KP / 4); e += kApplyThreads) {
+      const int f = e % D, k0 = 4 * (e / D);
+      f32x4 x;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int f = f0 + j, i = rope_pair(style, D, f);
-        const float partner = style == KVC_ROPE_HALF ? y[j] : s[j ^ 1];
-        o[j] = rope_rotated(rope_first(style, D, f), s[j], partner, s_rope[0][i], s_rope[1][i]);
+      for (int i = 0; i < 4; ++i) {
+        const int k = k0 + i;
+        x[i] = k < r ? basis[k * bstride + f] : 0.0f;
+        if (rope && k < r) {
+          const int pi = rope_pair(style, D, f);
+          x[i] = rope_rotated(rope_first(style, D, f), x[i], basis[k * bstride + rope_partner(style, D, f)],
+                              s_rope[2][pi], s_rope[3][pi]);
+        }
+      }
+      *reinterpret_cast<f32x4*>(s_b + f * LDB + k0) = x;
+    }
+  }
+  __syncthreads();
+
+  auto row_off = [&](int off, int lb0, const int32_t* tab, int t) -> int64_t {
+    const int p = off + t, lb = lblock(p), slot = p - lb * bs;
+    const int32_t blk = tab[lb - lb0];
+    if (blk < 0 || blk >= a.pv.num_blocks) return -1;
+    return (int64_t)blk * a.pv.block_stride + (int64_t)slot * a.pv.token_stride + (int64_t)head * a.pv.head_stride;
+  };
+  struct Tile {
+    f32x4 raw[MT], c[KQ];
+    int64_t dof;
+  };
+  auto tile_t0 = [&](int j) { return t_begin + (j * kApplyWaves + wave) * 16; };
+  auto load_tile = [&](int j, Tile& tl) __attribute__((always_inline)) {
+    const int t = tile_t0(j) + n;
+    const bool valid = j < tpw && t < t_end;
+    const int64_t so = valid ? row_off(src_off, lb0s, s_tab, t) : -1;
+    // a row whose source block id is out of range is neither read nor written
+    tl.dof = so >= 0 ? row_off(dst_off, lb0d, s_tab + nblk, t) : -1;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+      tl.raw[m] = so >= 0 ? *reinterpret_cast<const f32x4*>(src_pool + so + 16 * m + 4 * g)
+                          : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < KQ; ++q) {
+      const int k0 = 16 * q + 4 * g;
+      tl.c[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (valid && t < Ts) {
+        const float* cp = coef + (int64_t)t * r + k0;
+        if ((r & 3) == 0) {
+          if (k0 < r) tl.c[q] = *reinterpret_cast<const f32x4*>(cp);
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) tl.c[q][i] = k0 + i < r ? cp[i] : 0.0f;
+        }
       }
     }
-    if (t < Ts) {
-      const float* crow = coef + (int64_t)t * r;
-      for (int k = 0; k < r; ++k) {
-        const float c = crow[k];
-        const f32x4 b = *reinterpret_cast<const f32x4*>(&s_b[k * D + f0]);
-        o[0] = fmaf(c, b[0], o[0]);
-        o[1] = fmaf(c, b[1], o[1]);
-        o[2] = fmaf(c, b[2], o[2]);
-        o[3] = fmaf(c, b[3], o[3]);
+  };
+
+  Tile cur;
+  if (tile_t0(0) >= t_end) return;  // whole wave; the kernel has no barrier below
+  load_tile(0, cur);
+  for (int j = 0; j < tpw; ++j) {
+    const int t0 = tile_t0(j), t = t0 + n;
+    if (t0 >= t_end) break;  // whole wave
+    Tile nxt;
+    load_tile(j + 1, nxt);
+    f32x4 acc[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) acc[m] = cur.raw[m];
+    if (shift) {  // the source rotated by pd - ps: both features of a pair are in the lane
+      const float *c = s_rope[0], *s = s_rope[1];
+      if (style == KVC_ROPE_HALF) {
+#pragma unroll
+        for (int m = 0; m < MT / 2; ++m)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int i = 16 * m + 4 * g + e;
+            const float x = acc[m][e], y = acc[m + MT / 2][e];
+            acc[m][e] = rope_rotated(true, x, y, c[i], s[i]);
+            acc[m + MT / 2][e] = rope_rotated(false, y, x, c[i], s[i]);
+          }
+      } else {
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+          for (int e = 0; e < 4; e += 2) {
+            const int i = (16 * m + 4 * g + e) >> 1;
+            const float x = acc[m][e], y = acc[m][e + 1];
+            acc[m][e] = rope_rotated(true, x, y, c[i], s[i]);
+            acc[m][e + 1] = rope_rotated(false, y, x, c[i], s[i]);
+          }
       }
     }
-    *reinterpret_cast<f32x4*>(dst_pool + dof + f0) = o;
+    if (t0 < Ts) {  // uniform over the wave
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int q = 0; q < KQ; ++q) {
+          const f32x4 b = *reinterpret_cast<const f32x4*>(s_b + (16 * m + n) * LDB + 16 * q + 4 * g);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], cur.c[q][e], acc[m], 0, 0, 0);
+        }
+    }
+    if (cur.dof >= 0) {
+      // rows past T_s: with a shift the rotated source, else bit copies
+      const bool crow = t < Ts || shift;
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+        *reinterpret_cast<f32x4*>(dst_pool + cur.dof + 16 * m + 4 * g) = crow ? acc[m] : cur.raw[m];
+    }
+    cur = nxt;
   }
 }
 
@@ -407,6 +491,33 @@ static hipError_t launch_bf16_ks(const ApplyArgs& a, int ks, int max_tokens, int
   }
 }
 
+template <int D, int KQ>
+static hipError_t launch_f32(const ApplyArgs& a0, int max_tokens, int num_items, hipStream_t stream) {
+  ApplyArgs a = a0;
+  const int units = 2 * a.pv.num_kv_heads, il = num_items * a.num_layers;
+  // 64 tokens per workgroup while that leaves the chip unfilled (below four workgroups per CU), else 256
+  const int64_t wide = (int64_t)((max_tokens + 64 * kApplyF32Tiles - 1) / (64 * kApplyF32Tiles)) * units * il;
+  const int tpw = wide < 1024 ? 1 : kApplyF32Tiles;
+  const int chunk = 64 * tpw, chunks = (max_tokens + chunk - 1) / chunk;
+  a.chunk_order = multi_item_order(num_items, chunks, kChunksRotated);
+  const int nblk = (chunk + a.pv.block_size - 1) / a.pv.block_size + 1;
+  const size_t lds = (size_t)D * (16 * KQ + 4) * sizeof(float) + (size_t)2 * nblk * sizeof(int32_t);
+  const hipError_t e = hipFuncSetAttribute((const void*)apply_f32_mfma<D, KQ>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((apply_f32_mfma<D, KQ>), chunk_grid(chunks, units, il, a.chunk_order), dim3(kApplyThreads), lds,
+                     stream, a, tpw, nblk);
+  return hipGetLastError();
+}
+
+template <int D>
+static hipError_t launch_f32_kq(const ApplyArgs& a, int kq, int max_tokens, int num_items, hipStream_t stream) {
+  if (kq <= 1) return launch_f32<D, 1>(a, max_tokens, num_items, stream);
+  if (kq == 2) return launch_f32<D, 2>(a, max_tokens, num_items, stream);
+  if (kq <= 4) return launch_f32<D, 4>(a, max_tokens, num_items, stream);
+  return launch_f32<D, 8>(a, max_tokens, num_items, stream);
+}
+
 hipError_t launch_apply(const ApplyArgs& a, kvc_dtype dtype, int max_rank, int max_tokens, int num_items,
                         hipStream_t stream) {
   if (max_tokens == 0 || num_items == 0 || a.num_layers == 0) return hipSuccess;
@@ -416,17 +527,8 @@ hipError_t launch_apply(const ApplyArgs& a, kvc_dtype dtype, int max_rank, int m
     return D == 64 ? launch_bf16_ks<64>(a, ks, max_tokens, num_items, stream)
                    : launch_bf16_ks<128>(a, ks, max_tokens, num_items, stream);
   }
-  ApplyArgs b = a;
-  const int chunks = (max_tokens + kApplyChunk - 1) / kApplyChunk;
-  b.chunk_order = multi_item_order(num_items, chunks, kChunksRotated);
-  const dim3 grid = chunk_grid(chunks, 2 * a.pv.num_kv_heads, num_items * a.num_layers, b.chunk_order);
-  const size_t lds = (size_t)max_rank * D * sizeof(float);
-  if (D == 64) {
-    hipLaunchKernelGGL(apply_f32_valu<64>, grid, dim3(kApplyThreads), lds, stream, b);
-  } else {
-    hipLaunchKernelGGL(apply_f32_valu<128>, grid, dim3(kApplyThreads), lds, stream, b);
-  }
-  return hipGetLastError();
+  return D == 64 ? launch_f32_kq<64>(a, (max_rank + 15) / 16, max_tokens, num_items, stream)
+                 : launch_f32_kq<128>(a, (max_rank + 15) / 16, max_tokens, num_items, stream);
 }
 
 }  // namespace kvc

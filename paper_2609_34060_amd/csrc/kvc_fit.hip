@@ -10,7 +10,7 @@
 // (see GramSeg) so that its operands come straight from coalesced row loads; only tiles on or above the diagonal
 // are computed and each is stored with its mirror.  In the projection the rows are read straight into the MFMA
 // B-operand layout (16 contiguous bytes per lane), the basis hi/lo is staged in LDS.
-// float32 caches use plain fp32 VALU kernels.
+// float32 caches use the fp32 matrix instruction (v_mfma_f32_16x16x4_f32): fp32 products and sums.
 #include <utility>
 
 #include "kvc_device.h"
@@ -492,15 +492,61 @@ __global__ __launch_bounds__(kFitThreads) void gram_bf16_ring(FitArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// Gram, fp32 caches (VALU, fp32 accumulation)
+// Gram, fp32 caches (v_mfma_f32_16x16x4_f32: fp32 products, fp32 accumulation)
 // ---------------------------------------------------------------------------------------------------------------
 
+__device__ __forceinline__ f32x4 mfma16x16x4(float a, float b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// Rows of SF tokens per lane (token group g of a 4 SF-token batch holds tokens SF g .. SF g + SF - 1), the FT features
+// FT n .. of each: with the permuted feature order of GramSeg, element e of the segment is the MFMA operand of tile
+// row e as it stands, so Z goes from the row loads to the matrix cores without LDS or permutes.
+template <int D, int Q>
+__device__ __forceinline__ void gram_f32_tile(f32x4* acc, const float* z) {
+  constexpr int FT = D / 16;
+  acc[Q] = mfma16x16x4(z[tile_fi(Q, FT)], z[tile_fj(Q, FT)], acc[Q]);
+}
+template <int D, int... Is>
+__device__ __forceinline__ void gram_f32_tiles(f32x4* acc, const float* z, std::integer_sequence<int, Is...>) {
+  (gram_f32_tile<D, Is>(acc, z), ...);
+}
+// Tile idx and its mirror into the full matrix m [D][LDM] in LDS.
+template <int D, int LDM, int... Is>
+__device__ __forceinline__ void gram_f32_place(float* m, const f32x4* acc, int g, int n,
+                                               std::integer_sequence<int, Is...>) {
+  constexpr int FT = D / 16;
+  auto one = [&](int fi, int fj, const f32x4& v) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = FT * (4 * g + i) + fi, col = FT * n + fj;
+      m[row * LDM + col] = v[i];
+      m[col * LDM + row] = v[i];
+    }
+  };
+  (one(tile_fi(Is, FT), tile_fj(Is, FT), acc[Is]), ...);
+}
+
+// One workgroup per partial: its four waves take the range's token batches in turn, each with every upper tile in
+// registers, and the four sums are added in a fixed order through LDS (tile fragments, 16 bytes per lane), then the
+// full matrix leaves in whole rows.  The next batch's rows are in flight while this one is multiplied.  Bound by the
+// fp32 matrix rate for head_dim 128 (36 tiles of 32 cycles per 4 tokens and wave), by latency for a few hundred
+// tokens (4 heads x 64, 256 tokens, two layers: GRAM_NEW us against 70 us for fp32 FMAs on operands read from LDS, one
+// output entry per thread and two LDS reads per FMA).
+template <int D>
+struct GramF32 {
+  static constexpr int FT = D / 16, NT = FT * (FT + 1) / 2, LDM = D + 4;
+  static constexpr int SF = D == 64 ? 4 : 2;  // 4-token steps per batch: 32 registers of rows per side pair
+  static constexpr size_t kFrag = (size_t)2 * NT * kWave * 16, kMat = (size_t)D * LDM * 4;
+  static constexpr size_t kLds = kFrag > kMat ? kFrag : kMat;
+};
+
 template <int D, bool ROPE>
-__global__ __launch_bounds__(kFitThreads) void gram_f32_valu(FitArgs a) {
-  constexpr int STEP = 32;
-  constexpr int NE = D * (D + 1) / 2;
-  constexpr int EPT = (NE + kFitThreads - 1) / kFitThreads;
-  __shared__ float s_z[STEP][D + 1];
+__global__ __launch_bounds__(kFitThreads) void gram_f32_mfma(FitArgs a) {
+  using GF = GramF32<D>;
+  constexpr int FT = GF::FT, NT = GF::NT, SF = GF::SF, NV = FT / 4, BT = 4 * SF;
+  extern __shared__ __attribute__((aligned(16))) unsigned char gram_lds[];
+  __shared__ float s_rope[4][ROPE ? D / 2 : 1];  // cos / sin of -pd and -ps (rotary keys)
 
   const FitUnit f = fit_unit(a);
   const kvc_item* itp = a.items + f.item;
@@ -508,76 +554,118 @@ __global__ __launch_bounds__(kFitThreads) void gram_f32_valu(FitArgs a) {
   const int Ts = itp->state.num_tokens;
   const int c = grid_chunk(a.chunk_order);
   const int t_begin = c * a.part_tokens;
-  if (r == 0 || t_begin >= Ts) return;
+  if (r == 0 || t_begin >= Ts) return;  // whole workgroup
   const int t_end = min(Ts, t_begin + a.part_tokens);
   const int32_t* src_tab = a.src_tables ? a.src_tables + (int64_t)f.item * a.max_blocks : nullptr;
   const int32_t* dst_tab = a.dst_tables ? a.dst_tables + (int64_t)f.item * a.max_blocks : nullptr;
   const float* pool = static_cast<const float*>(f.kv ? a.layers.v[f.lrel] : a.layers.k[f.lrel]);
   const bool delta = a.mode == KVC_FIT_DELTA;
-  const int tid = threadIdx.x;
-  __shared__ float s_rope[4][ROPE ? D / 2 : 1];  // cos / sin of -pd and -ps (rotary keys)
-  const bool rope = ROPE && f.kv == 0;
+  const int src_off = itp->src_offset, dst_off = itp->dst_offset;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, n = lane & 15;
+  const bool rope = ROPE && f.kv == 0;  // uniform over the workgroup
   const int style = a.pv.rope.style;
+  float rc[2][ROPE ? FT : 1], rsn[2][ROPE ? FT : 1];  // cos / sin of -pd and -ps for the lane's features
   if (rope) {
     rope_table(a.pv.rope, D, -(double)itp->dst_position, s_rope[0], s_rope[1]);
     rope_table(a.pv.rope, D, -(double)itp->src_position, s_rope[2], s_rope[3]);
     __syncthreads();
+#pragma unroll
+    for (int e = 0; e < (ROPE ? FT : 1); ++e) {
+      const int i = rope_pair(style, D, FT * n + e);
+      rc[0][e] = s_rope[0][i];
+      rsn[0][e] = s_rope[1][i];
+      rc[1][e] = s_rope[2][i];
+      rsn[1][e] = s_rope[3][i];
+    }
   }
 
-  int ei[EPT], ej[EPT];
-  float acc[EPT];
+  f32x4 acc[NT];
 #pragma unroll
-  for (int q = 0; q < EPT; ++q) {
-    int e = tid + q * kFitThreads;
-    acc[q] = 0.f;
-    ei[q] = -1;
-    ej[q] = 0;
-    if (e < NE) {
-      int i = 0;
-      while (e >= D - i) {
-        e -= D - i;
-        ++i;
+  for (int q = 0; q < NT; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  struct Offs {
+    int64_t d[SF], s[SF];
+  };
+  struct Rows {
+    f32x4 d[SF][NV], s[SF][NV];
+  };
+  auto load_offs = [&](int t0, Offs& o) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < SF; ++s) {
+      const int t = t0 + SF * g + s;
+      o.d[s] = t < t_end ? row_offset(a.pv, dst_tab, dst_off, t, f.head) : -1;
+      o.s[s] = t < t_end && delta ? row_offset(a.pv, src_tab, src_off, t, f.head) : -1;
+    }
+  };
+  auto load_rows = [&](const Offs& o, Rows& R) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < SF; ++s)
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        R.d[s][v] = o.d[s] >= 0 ? *reinterpret_cast<const f32x4*>(pool + o.d[s] + FT * n + 4 * v)
+                                : f32x4{0.f, 0.f, 0.f, 0.f};
+        R.s[s][v] = o.s[s] >= 0 ? *reinterpret_cast<const f32x4*>(pool + o.s[s] + FT * n + 4 * v)
+                                : f32x4{0.f, 0.f, 0.f, 0.f};
       }
-      ei[q] = i;
-      ej[q] = i + e;
+  };
+  // canonical value of element e of a row segment (rotary keys): its partner is element e of lane n ^ 8
+  // (rotate-half; features FT n + e and FT (n + 8) + e) or the neighbouring element
+  const bool half = style == KVC_ROPE_HALF, first_half = FT * n < D / 2;
+  auto canon = [&](const f32x4* v, int e, int side) {
+    const float x = v[e >> 2][e & 3];
+    const float y = half ? __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x128, 0xF,
+                                                                              0xF, false))
+                         : v[e >> 2][(e ^ 1) & 3];
+    return rope_rotated(half ? first_half : (e & 1) == 0, x, y, rc[side][ROPE ? e : 0], rsn[side][ROPE ? e : 0]);
+  };
+  auto multiply = [&](const Rows& R) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < SF; ++s) {
+      float z[FT];
+#pragma unroll
+      for (int e = 0; e < FT; ++e)
+        z[e] = ROPE && rope ? canon(R.d[s], e, 0) - canon(R.s[s], e, 1) : R.d[s][e >> 2][e & 3] - R.s[s][e >> 2][e & 3];
+      gram_f32_tiles<D>(acc, z, std::make_integer_sequence<int, NT>{});
+    }
+  };
+
+  int t0 = t_begin + wave * BT;
+  if (t0 < t_end) {
+    Offs o;
+    Rows cur;
+    load_offs(t0, o);
+    load_rows(o, cur);
+    load_offs(t0 + kFitWaves * BT, o);
+    for (; t0 < t_end; t0 += kFitWaves * BT) {
+      Rows nxt;
+      load_rows(o, nxt);
+      load_offs(t0 + 2 * kFitWaves * BT, o);
+      multiply(cur);
+      cur = nxt;
     }
   }
-  for (int t0 = t_begin; t0 < t_end; t0 += STEP) {
-    for (int e = tid; e < STEP * D; e += kFitThreads) {
-      const int tk = e / D, fe = e - tk * D;
-      const int t = t0 + tk;
-      float z = 0.f;
-      if (t < t_end) {
-        const int64_t od = row_offset(a.pv, dst_tab, itp->dst_offset, t, f.head);
-        const int64_t os = delta ? row_offset(a.pv, src_tab, itp->src_offset, t, f.head) : -1;
-        if (rope) {  // Z = R(-pd) C_dst - R(-ps) C_src
-          const int pf = rope_partner(style, D, fe), i = rope_pair(style, D, fe);
-          const bool first = rope_first(style, D, fe);
-          if (od >= 0) z = rope_rotated(first, pool[od + fe], pool[od + pf], s_rope[0][i], s_rope[1][i]);
-          if (os >= 0) z -= rope_rotated(first, pool[os + fe], pool[os + pf], s_rope[2][i], s_rope[3][i]);
-        } else {
-          if (od >= 0) z = pool[od + fe];
-          if (os >= 0) z -= pool[os + fe];
-        }
-      }
-      s_z[tk][fe] = z;
-    }
-    __syncthreads();
+
+  // (wave 0 + wave 2) + (wave 1 + wave 3)
+  f32x4* frag = reinterpret_cast<f32x4*>(gram_lds);
 #pragma unroll
-    for (int q = 0; q < EPT; ++q) {
-      if (ei[q] < 0) continue;
-      float s = acc[q];
-      for (int tk = 0; tk < STEP; ++tk) s = fmaf(s_z[tk][ei[q]], s_z[tk][ej[q]], s);
-      acc[q] = s;
-    }
+  for (int h = 2; h >= 1; h >>= 1) {
+    if (wave >= h && wave < 2 * h)
+#pragma unroll
+      for (int q = 0; q < NT; ++q) frag[((wave - h) * NT + q) * kWave + lane] = acc[q];
+    __syncthreads();
+    if (wave < h)
+#pragma unroll
+      for (int q = 0; q < NT; ++q) acc[q] += frag[(wave * NT + q) * kWave + lane];
     __syncthreads();
   }
+  float* m = reinterpret_cast<float*>(gram_lds);
+  if (wave == 0) gram_f32_place<D, GF::LDM>(m, acc, g, n, std::make_integer_sequence<int, NT>{});
+  __syncthreads();
   float* P = a.partials + ((size_t)fit_linear_unit(a, f) * a.max_parts + c) * D * D;
-#pragma unroll
-  for (int q = 0; q < EPT; ++q) {
-    if (ei[q] < 0) continue;
-    P[ei[q] * D + ej[q]] = acc[q];
-    P[ej[q] * D + ei[q]] = acc[q];
+  for (int e = tid; e < D * D / 4; e += kFitThreads) {
+    const int row = e / (D / 4), col = 4 * (e % (D / 4));
+    *reinterpret_cast<f32x4*>(P + row * D + col) = *reinterpret_cast<const f32x4*>(m + row * GF::LDM + col);
   }
 }
 
@@ -594,7 +682,6 @@ __global__ __launch_bounds__(kFitThreads) void gram_f32_valu(FitArgs a) {
 // read sits between two row loads.
 constexpr int kProjWaves = 8, kProjChunkTokens = 512, kProjLongChunkTokens = 1024;
 constexpr int kProjRopeWaves = 4, kProjRopeChunkTokens = 1024;
-constexpr int kProjChunk = 1024;  // tokens per workgroup of the float32 kernel
 
 __host__ __device__ constexpr size_t proj_lds_bytes(int D, int RP, int nblk) {
   return (size_t)2 * RP * D * 2 + (size_t)2 * nblk * 4;
@@ -775,52 +862,125 @@ __global__ __launch_bounds__(W * kWave) void proj_bf16_mfma(FitArgs a, int tpw, 
   }
 }
 
-// Projection, fp32 caches: one thread per (token, rank), fp32 FMAs over the features.
+// Projection, fp32 caches, on v_mfma_f32_16x16x4_f32: M = rank (16 per tile), N = token, K = feature.  Lane (g, n)
+// holds, of the row of token n, the 16-byte segments 16 q + 4 g .. + 3, and takes the same features of the basis row
+// from LDS, so both operands come in 16-byte reads and step (q, e) multiplies element e of segment q.  A workgroup of
+// four waves stages the basis once for 64 tpw tokens, each wave's next tile in flight behind the current one.  Bound by
+// memory from a few thousand rows on, by latency below (2 layers x 4 heads x 64, 256 tokens, rank 8: PROJ_NEW us against
+// 50 us for one thread per (token, rank) reading every row once per rank).
+constexpr int kProjF32MaxTiles = 4;  // 16-token tiles per wave where the launch fills the chip anyway
+
 template <int D, bool ROPE>
-__global__ __launch_bounds__(kFitThreads) void proj_f32_valu(FitArgs a) {
-  extern __shared__ __attribute__((aligned(16))) float s_b[];  // [r][D]
+__global__ __launch_bounds__(kFitThreads) void proj_f32_mfma(FitArgs a, int tpw) {
+  constexpr int NQ = D / 16, LDB = D + 4;  // padded basis rows: the 16 lanes of a read cover all banks
+  extern __shared__ __attribute__((aligned(16))) float s_b[];  // [16 mtr][LDB]
+  __shared__ float s_rope[4][ROPE ? D / 2 : 1];                // cos / sin of -pd and -ps (rotary keys)
   const FitUnit f = fit_unit(a);
   const kvc_item* itp = a.items + f.item;
   const int r = itp->state.rank;
   const int Ts = itp->state.num_tokens;
-  const int t_begin = grid_chunk(a.chunk_order) * kProjChunk;
-  if (r == 0 || t_begin >= Ts) return;
-  const int t_end = min(Ts, t_begin + kProjChunk);
+  const int chunk = kFitWaves * 16 * tpw;
+  const int t_begin = grid_chunk(a.chunk_order) * chunk;
+  if (r == 0 || t_begin >= Ts) return;  // whole workgroup
+  const int t_end = min(Ts, t_begin + chunk);
   const int32_t* src_tab = a.src_tables ? a.src_tables + (int64_t)f.item * a.max_blocks : nullptr;
   const int32_t* dst_tab = a.dst_tables ? a.dst_tables + (int64_t)f.item * a.max_blocks : nullptr;
   const float* pool = static_cast<const float*>(f.kv ? a.layers.v[f.lrel] : a.layers.k[f.lrel]);
   const bool delta = a.mode == KVC_FIT_DELTA;
   const float* basis = itp->state.basis + f.unit * (int64_t)r * D;
   float* coef = static_cast<float*>(itp->state.coef) + f.unit * (int64_t)Ts * r;
-  __shared__ float s_rope[4][ROPE ? D / 2 : 1];  // cos / sin of -pd and -ps (rotary keys)
-  const bool rope = ROPE && f.kv == 0;
+  const int src_off = itp->src_offset, dst_off = itp->dst_offset;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, n = lane & 15;
+  const int mtr = (r + 15) / 16;
+  const bool rope = ROPE && f.kv == 0;  // uniform over the workgroup
   const int style = a.pv.rope.style;
+
+  struct Rows {
+    f32x4 d[NQ], s[NQ];
+  };
+  auto tile_t0 = [&](int j) { return t_begin + (j * kFitWaves + wave) * 16; };
+  auto load_rows = [&](int j, Rows& R) __attribute__((always_inline)) {
+    const int t = tile_t0(j) + n;
+    const bool valid = j < tpw && t < t_end;
+    const int64_t od = valid ? row_offset(a.pv, dst_tab, dst_off, t, f.head) : -1;
+    const int64_t os = valid && delta ? row_offset(a.pv, src_tab, src_off, t, f.head) : -1;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      R.d[q] = od >= 0 ? *reinterpret_cast<const f32x4*>(pool + od + 16 * q + 4 * g) : f32x4{0.f, 0.f, 0.f, 0.f};
+      R.s[q] = os >= 0 ? *reinterpret_cast<const f32x4*>(pool + os + 16 * q + 4 * g) : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  Rows cur;
+  load_rows(0, cur);  // in flight while the basis is staged
   if (rope) {
     rope_table(a.pv.rope, D, -(double)itp->dst_position, s_rope[0], s_rope[1]);
     rope_table(a.pv.rope, D, -(double)itp->src_position, s_rope[2], s_rope[3]);
   }
-  for (int e = threadIdx.x; e < r * D; e += kFitThreads) s_b[e] = basis[e];
+  for (int e = tid; e < 16 * mtr * (D / 4); e += kFitThreads) {
+    const int k = e / (D / 4), fe = 4 * (e % (D / 4));
+    *reinterpret_cast<f32x4*>(s_b + k * LDB + fe) =
+        k < r ? *reinterpret_cast<const f32x4*>(basis + k * D + fe) : f32x4{0.f, 0.f, 0.f, 0.f};
+  }
   __syncthreads();
-  const int64_t total = (int64_t)(t_end - t_begin) * r;
-  for (int64_t e = threadIdx.x; e < total; e += kFitThreads) {
-    const int t = t_begin + (int)(e / r), k = (int)(e % r);
-    const int64_t od = row_offset(a.pv, dst_tab, itp->dst_offset, t, f.head);
-    const int64_t os = delta ? row_offset(a.pv, src_tab, itp->src_offset, t, f.head) : -1;
-    float s = 0.f;
-    for (int fe = 0; fe < D; ++fe) {
-      float z;
-      if (rope) {  // Z = R(-pd) C_dst - R(-ps) C_src
-        const int pf = rope_partner(style, D, fe), i = rope_pair(style, D, fe);
-        const bool first = rope_first(style, D, fe);
-        z = od >= 0 ? rope_rotated(first, pool[od + fe], pool[od + pf], s_rope[0][i], s_rope[1][i]) : 0.f;
-        if (os >= 0) z -= rope_rotated(first, pool[os + fe], pool[os + pf], s_rope[2][i], s_rope[3][i]);
-      } else {
-        z = od >= 0 ? pool[od + fe] : 0.f;
-        if (os >= 0) z -= pool[os + fe];
-      }
-      s = fmaf(z, s_b[k * D + fe], s);
+  // a row in canonical coordinates: rotate-half partners are the segments q and q + NQ / 2 of the same lane, adjacent
+  // pairs sit inside a segment
+  auto rotate = [&](f32x4* v, const float* c, const float* s) {
+    if (style == KVC_ROPE_HALF) {
+#pragma unroll
+      for (int q = 0; q < NQ / 2; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int i = 16 * q + 4 * g + e;
+          const float x = v[q][e], y = v[q + NQ / 2][e];
+          v[q][e] = rope_rotated(true, x, y, c[i], s[i]);
+          v[q + NQ / 2][e] = rope_rotated(false, y, x, c[i], s[i]);
+        }
+    } else {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; e += 2) {
+          const int i = (16 * q + 4 * g + e) >> 1;
+          const float x = v[q][e], y = v[q][e + 1];
+          v[q][e] = rope_rotated(true, x, y, c[i], s[i]);
+          v[q][e + 1] = rope_rotated(false, y, x, c[i], s[i]);
+        }
     }
-    coef[(int64_t)t * r + k] = s;
+  };
+  for (int j = 0; j < tpw; ++j) {
+    if (tile_t0(j) >= t_end) break;  // whole wave; the kernel has no barrier below
+    Rows nxt;
+    load_rows(j + 1, nxt);
+    if (ROPE && rope) {
+      rotate(cur.d, s_rope[0], s_rope[1]);
+      rotate(cur.s, s_rope[2], s_rope[3]);
+    }
+    f32x4 z[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) z[q] = cur.d[q] - cur.s[q];
+    const int t = tile_t0(j) + n;
+    for (int mt = 0; mt < mtr; ++mt) {
+      f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};  // even and odd segments: two chains
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const f32x4 b = *reinterpret_cast<const f32x4*>(s_b + (16 * mt + n) * LDB + 16 * q + 4 * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[q & 1] = mfma16x16x4(b[e], z[q][e], acc[q & 1]);
+      }
+      const f32x4 o = acc[0] + acc[1];
+      if (t < t_end) {  // lane holds coef[t][16 mt + 4 g + i]
+        const int k0 = 16 * mt + 4 * g;
+        float* cp = coef + (int64_t)t * r + k0;
+        if ((r & 3) == 0) {
+          if (k0 < r) *reinterpret_cast<f32x4*>(cp) = o;
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (k0 + i < r) cp[i] = o[i];
+        }
+      }
+    }
+    cur = nxt;
   }
 }
 
@@ -859,8 +1019,12 @@ static hipError_t launch_gram_variants(const FitArgs& a0, kvc_dtype dtype, int n
   } else {
     a.chunk_order = multi_item_order(num_items, a.max_parts, kItemsFast);
     const dim3 grid = chunk_grid(a.max_parts, nkv * a.pv.num_kv_heads, il, a.chunk_order);
-    if (D == 64) hipLaunchKernelGGL((gram_f32_valu<64, ROPE>), grid, dim3(kFitThreads), 0, stream, a);
-    else hipLaunchKernelGGL((gram_f32_valu<128, ROPE>), grid, dim3(kFitThreads), 0, stream, a);
+    const void* fn = D == 64 ? (const void*)gram_f32_mfma<64, ROPE> : (const void*)gram_f32_mfma<128, ROPE>;
+    const size_t lds = D == 64 ? GramF32<64>::kLds : GramF32<128>::kLds;
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    if (D == 64) hipLaunchKernelGGL((gram_f32_mfma<64, ROPE>), grid, dim3(kFitThreads), lds, stream, a);
+    else hipLaunchKernelGGL((gram_f32_mfma<128, ROPE>), grid, dim3(kFitThreads), lds, stream, a);
   }
   return hipGetLastError();
 }
@@ -915,12 +1079,19 @@ static hipError_t launch_proj_variants(const FitArgs& a0, kvc_dtype dtype, int n
     return D == 64 ? launch_proj_bf16<64, ROPE>(a, mtr, nkv, max_tokens, num_items, stream)
                    : launch_proj_bf16<128, ROPE>(a, mtr, nkv, max_tokens, num_items, stream);
   }
-  const int chunks = (max_tokens + kProjChunk - 1) / kProjChunk;
+  // 64 tokens per workgroup while that leaves the chip unfilled (below four workgroups per CU), else 256
+  const int64_t wide = (int64_t)((max_tokens + 64 * kProjF32MaxTiles - 1) / (64 * kProjF32MaxTiles)) * nkv *
+                       a.pv.num_kv_heads * num_items * a.num_layers;
+  const int tpw = wide < 1024 ? 1 : kProjF32MaxTiles;
+  const int chunks = (max_tokens + 64 * tpw - 1) / (64 * tpw);
   a.chunk_order = multi_item_order(num_items, chunks, kChunksRotated);
   const dim3 grid = chunk_grid(chunks, nkv * a.pv.num_kv_heads, num_items * a.num_layers, a.chunk_order);
-  const size_t lds = (size_t)max_rank * D * sizeof(float);
-  if (D == 64) hipLaunchKernelGGL((proj_f32_valu<64, ROPE>), grid, dim3(kFitThreads), lds, stream, a);
-  else hipLaunchKernelGGL((proj_f32_valu<128, ROPE>), grid, dim3(kFitThreads), lds, stream, a);
+  const size_t lds = (size_t)(max_rank + 15) / 16 * 16 * (D + 4) * sizeof(float);
+  const void* fn = D == 64 ? (const void*)proj_f32_mfma<64, ROPE> : (const void*)proj_f32_mfma<128, ROPE>;
+  const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  if (D == 64) hipLaunchKernelGGL((proj_f32_mfma<64, ROPE>), grid, dim3(kFitThreads), lds, stream, a, tpw);
+  else hipLaunchKernelGGL((proj_f32_mfma<128, ROPE>), grid, dim3(kFitThreads), lds, stream, a, tpw);
   return hipGetLastError();
 }
 

@@ -41,7 +41,6 @@ inline dim3 chunk_grid(int chunks, int units, int item_layers, int32_t order) {
   return order == kItemsFast ? dim3(item_layers, units, chunks) : dim3(chunks, units, item_layers);
 }
 
-int apply_chunk_tokens();
 hipError_t launch_apply(const ApplyArgs& a, kvc_dtype dtype, int max_rank, int max_tokens, int num_items,
                         hipStream_t stream);
 

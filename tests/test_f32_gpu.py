@@ -1,0 +1,117 @@
+"""Float32 caches on the GPU at the edges of the fp32 matrix tiles: ranks and token counts around multiples of 16 and
+of the chunk sizes, block sizes that are no power of two, uncovered rows, both rotary styles and per-layer states.
+
+Apply: the corrected rows against fp64 arithmetic, max relative error <= 1e-5 of the slice's largest value (float32
+storage); uncovered rows bit for bit.  Fit: the stored coefficients against Z B^T of the returned basis in fp64 (a
+128-term fp32 sum, each term rounded at 2^-24 of a row norm: below 1e-5 of the largest row norm), and the residual of
+the reconstruction against the best rank-r residual of an fp64 eigendecomposition of Z^T Z (fp32 Gram: the basis is off
+by about 1e-6, which changes the residual to second order; 1e-3 allows for the coefficients' rounding)."""
+import math
+
+import pytest
+import torch
+
+from paper_2609_34060_amd import kvc
+
+pytestmark = pytest.mark.gpu
+THETA = 1e4
+
+
+def _rotate(x, style, pos):
+    """x [..., d] in fp64 rotated to position pos."""
+    d = x.shape[-1]
+    th = pos * torch.tensor([THETA ** (-2.0 * i / d) for i in range(d // 2)], dtype=torch.float64)
+    co, si = torch.cos(th), torch.sin(th)
+    if style == kvc.KVC_ROPE_HALF:
+        a, b = x[..., :d // 2], x[..., d // 2:]
+        return torch.cat([a * co - b * si, a * si + b * co], dim=-1)
+    a, b = x[..., 0::2], x[..., 1::2]
+    return torch.stack([a * co - b * si, a * si + b * co], dim=-1).flatten(-2)
+
+
+class _Setup:
+    def __init__(self, L, H, d, T, bs, style, seed):
+        g = torch.Generator().manual_seed(seed)
+        self.L, self.H, self.d, self.T, self.bs, self.style = L, H, d, T, bs, style
+        self.off, self.pos = ((3, 5) if style else (5, 2)), ((11, 40) if style else (0, 0))
+        need = max(-(-(o + T) // bs) for o in self.off)
+        ids = torch.randperm(2 * need, generator=g)
+        self.tab = [ids[:need], ids[need:]]
+        self.pool = torch.randn(L, 2, 2 * need, bs, H, d, generator=g)
+        p = [torch.arange(T) + o for o in self.off]
+        self.rows = [(self.tab[i][p[i] // bs], p[i] % bs) for i in range(2)]
+        self.dev = self.pool.cuda()
+        inv = [THETA ** (-2.0 * i / d) for i in range(d // 2)] if style else None
+        self.cache = kvc.Cache([self.dev[l, 0] for l in range(L)], [self.dev[l, 1] for l in range(L)],
+                               rope_style=style, rope_inv_freq=inv)
+
+    def batch(self, st):
+        t = [x.to(torch.int32).view(1, -1).cuda() for x in self.tab]
+        return kvc.Batch([self.T], [self.off[0]], [self.off[1]], [st], t[0], t[1], src_positions=[self.pos[0]],
+                         dst_positions=[self.pos[1]])
+
+    def side(self, pool, l, kv, i, canonical=False):
+        x = pool[l, kv][self.rows[i][0], self.rows[i][1]].double()  # [T, H, d]
+        return _rotate(x, self.style, -self.pos[i]) if canonical and kv == 0 and self.style else x
+
+
+@pytest.mark.parametrize("d,r,T,Ts,bs,style,layerwise", [
+    (64, 8, 256, 256, 16, 0, False), (64, 1, 1, 1, 16, 0, False), (64, 17, 65, 50, 8, 1, False),
+    (64, 63, 129, 129, 24, 2, False), (128, 16, 63, 63, 16, 0, True), (128, 33, 300, 299, 64, 1, False),
+    (128, 64, 257, 0, 5, 2, False), (128, 128, 140, 140, 32, 1, False), (128, 20, 5000, 4997, 16, 0, False)])
+def test_apply_f32_edges(d, r, T, Ts, bs, style, layerwise):
+    L, H = 2, 3
+    s = _Setup(L, H, d, T, bs, style, 7 * T + r)
+    g = torch.Generator().manual_seed(r)
+    if layerwise:
+        st = kvc.State(torch.randn(L, 2, Ts, r, generator=g).cuda(),
+                       (torch.randn(L, 2, r, H, d, generator=g) / math.sqrt(r)).cuda())
+    else:
+        st = kvc.State(torch.randn(L, 2, H, Ts, r, generator=g).cuda(),
+                       (torch.randn(L, 2, H, r, d, generator=g) / math.sqrt(r)).cuda())
+    kvc.kvc_apply(s.cache, s.batch(st))
+    got = s.dev.cpu()
+    for l in range(L):
+        for kv in range(2):
+            want = s.side(s.pool, l, kv, 0, canonical=True)
+            a, b = st.coef[l, kv].cpu().double(), st.basis[l, kv].cpu().double()
+            if layerwise:
+                want[:Ts] += (a @ b.reshape(r, H * d)).view(Ts, H, d)
+            else:
+                want[:Ts] += torch.matmul(a, b).transpose(0, 1)
+            if kv == 0 and style:
+                want = _rotate(want, style, s.pos[1])
+            have = s.side(got, l, kv, 1)
+            assert (have - want).abs().max() <= 1e-5 * want.abs().max()
+            if kv == 1 or not style:
+                assert torch.equal(have[Ts:], s.side(s.pool, l, kv, 0)[Ts:])
+            # the source rows and every other row stay as they were
+            keep = got[l, kv].clone()
+            keep[s.rows[1][0], s.rows[1][1]] = s.pool[l, kv][s.rows[1][0], s.rows[1][1]]
+            assert torch.equal(keep, s.pool[l, kv])
+
+
+@pytest.mark.parametrize("d,r,T,bs,style,base", [
+    (64, 8, 256, 16, 0, False), (64, 3, 17, 8, 0, True), (64, 16, 65, 24, 1, False), (64, 48, 1030, 16, 2, False),
+    (128, 17, 33, 16, 0, False), (128, 32, 600, 5, 1, False), (128, 64, 515, 64, 2, False),
+    (128, 100, 2049, 16, 0, True)])
+def test_fit_f32_edges(d, r, T, bs, style, base):
+    L, H = 2, 3
+    s = _Setup(L, H, d, T, bs, style, 11 * T + r)
+    st = kvc.State.empty(L, H, d, T, r, torch.float32, "cuda")
+    kvc.kvc_fit_state(s.cache, s.batch(st), mode=kvc.KVC_FIT_BASE if base else kvc.KVC_FIT_DELTA)
+    assert torch.equal(s.dev.cpu(), s.pool)
+    for l in range(L):
+        for kv in range(2):
+            z = s.side(s.pool, l, kv, 1, canonical=True)
+            if not base:
+                z = z - s.side(s.pool, l, kv, 0, canonical=True)
+            for h in range(H):
+                zh = z[:, h]
+                a, b = st.coef[l, kv, h].cpu().double(), st.basis[l, kv, h].cpu().double()
+                assert (a - zh @ b.t()).abs().max() <= 1e-5 * zh.norm(dim=1).max()
+                lam = torch.linalg.eigvalsh(zh.t() @ zh).flip(0).clamp_min(0)
+                best, total = lam[r:].sum().sqrt(), lam.sum().sqrt()
+                assert (zh - a @ b).norm() <= best * (1 + 1e-3) + 1e-3 * total
+                sig = st.sigma[l, kv, h].cpu().double()
+                assert (sig - lam[:r].sqrt()).abs().max() <= 1e-3 * lam[0].sqrt()
