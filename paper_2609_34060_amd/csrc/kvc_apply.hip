@@ -266,7 +266,7 @@ __global__ __launch_bounds__(W * kWave) void apply_bf16_mfma(ApplyArgs a, int tp
 // B^T read from LDS in the same order (rows padded by 4 ranks: the 16 lanes of a read cover all banks).  A workgroup of
 // four waves stages the basis and the table slices once for 64 tpw tokens; the next tile's loads are in flight while
 // this one is finished.  Latency-bound at a few hundred tokens (2 layers x 4 heads x 64, 256 tokens, rank 8:
-// APPLY_NEW us against 15.7 us for one FMA chain per feature with a dependent table, coefficient and row load per token),
+// 6.6 us against 15.7 us for one FMA chain per feature with a dependent table, coefficient and row load per token),
 // memory-bound from a few thousand on.
 template <int D, int KQ>
 __global__ __launch_bounds__(kApplyThreads) void apply_f32_mfma(ApplyArgs a, int tpw, int nblk) {

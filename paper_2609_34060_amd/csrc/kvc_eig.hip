@@ -1,11 +1,11 @@
 // Top-r eigenpairs of the per-unit d x d Gram matrices in fp64: the right singular vectors R_r and singular values
-// of Eq. 7 (Z^T Z = R Sigma^2 R^T).  One workgroup of 1024 threads per (layer, K/V, head) unit:
+// of Eq. 7 (Z^T Z = R Sigma^2 R^T).  One workgroup of 512 threads per (layer, K/V, head) unit:
 //   1. G = sum of the unit's fp32 partial Grams in a fixed order in fp64 (or a dense fp64 matrix), into LDS.
-//   2. Householder tridiagonalisation G = Q T Q^T in fp64 arithmetic; the trailing matrix is kept in LDS in fp32
+//   2. Householder tridiagonalisation G = Q T Q^T in fp64 arithmetic; the trailing matrix is kept in registers in fp32
 //      (the Gram itself carries fp32 accuracy), which lets two units share a CU; the reflectors go to the workspace.
 //   3. Multisection bisection with Sturm counts for the r largest eigenvalues of T: a first step shared by all
-//      targets (every lane's shifts cut the whole interval), then groups of lanes per eigenvalue, kBisShifts
-//      shifts per lane, one ballot per shift.
+//      targets (the lanes' shifts cut the whole interval), then groups of lanes per eigenvalue, one shift per lane
+//      and one ballot per step.
 //   4. Inverse iteration on T (LDL^T without pivoting, tiny pivots replaced) from pseudo-random starts, one lane
 //      per eigenvector; then modified Gram-Schmidt within each cluster of close eigenvalues.  Vectors of tightly
 //      clustered eigenvalues come out as an orthonormal basis of the cluster's invariant subspace (where the SVD
@@ -20,11 +20,10 @@
 
 namespace kvc {
 
-constexpr int kEigThreads = 1024;
+constexpr int kEigThreads = 512;
 constexpr int kEigWaves = kEigThreads / kWave;
 constexpr int kReflChunk = 16;  // reflectors staged in LDS per back-transformation chunk
 constexpr int kInvBatch = 32;   // eigenvectors per inverse-iteration batch (one lane each)
-constexpr int kBisShifts = 2;   // Sturm counts per lane and bisection step (even: whole int2 slices below)
 // Inverse-iteration solves per eigenvector: with lambda within about 2^-24 of the spectrum's width, each solve
 // shrinks the other eigenvectors' components by that error over their gap, so two solves leave a residual far
 // below the fp32 rounding of the reduced matrix (about 1e-11 of the width in an fp64 simulation of the recurrence
@@ -152,53 +151,89 @@ __device__ __forceinline__ void reflector_scalars(double x0, double s, double* o
   out[2] = nrm == 0.0 ? 0.0 : recip(nrm * (nrm + fabs(x0)));
 }
 
-// Numbers of eigenvalues of T below each of the M shifts x[m]: the ratio form of the Sturm sequence, q_i = (a_i - x)
-// - b_{i-1}^2 / q_{i-1}, with the hardware reciprocal (relative error below 2^-24, measured on random fp64 inputs)
-// and IEEE infinities in place of a pivot guard: a zero pivot makes the next one -inf (counted), and the one after
-// that is plain a - x again, the same count the classical replacement of tiny pivots gives.  b^2 is floored at the
-// smallest normal number so that b^2 times an infinite reciprocal is never 0 * inf.  Each count is exact for T with
-// every b^2 perturbed by at most 2^-24 relative, below the perturbation fp32 storage of the matrix carries.  The M
-// recurrences are independent, so their latencies overlap, and they share the loads of T.
-template <int N, int M>
-__device__ __forceinline__ void sturm_counts(const double* sa, const double* sb2, const double* x, int* cnt) {
-  double q[M];
+// Number of eigenvalues of T below the shift x: sign changes of the leading minors p_i = (a_i - x) p_{i-1}
+// - b_{i-1}^2 p_{i-2} (two multiply-adds per step and shift, no division: the reciprocal of the ratio form costs several
+// times as much as the rest of its step).  T is scaled so that its norm is in [1, 2): |a_i - x| and b^2 stay below 8, so
+// eight steps grow the pair by less than 2^32, and with b^2 floored at 2^-120 (a perturbation of 2^-60 of the norm) eight
+// steps shrink it by 2^-480 at the most; every eight steps the pair is scaled by a power of two back to [1, 2), so
+// neither end of the range is reached.  A minor that comes out zero counts as positive, and the next one is then
+// -b^2 p_{i-2} with the opposite sign of p_{i-2}: one change over the two steps, whatever the sign before.  Each computed
+// count is exact for a T whose entries are off by a few 2^-53.  The signs are shifted into a word (one instruction a
+// step) and the changes counted every 32 steps.  512 units of N = 128, rank 16: bisection 54 us in the ratio form with
+// two shifts per lane, 17 us so.
+template <int N>
+__device__ __forceinline__ int sturm_count(const double* sa, const double* sb2, double x) {
+  double p0 = 0.0, p1 = 1.0;     // p_{i-2}, p_{i-1}
+  uint32_t sg = 0, last = 0;     // signs of the last 32 minors, newest lowest; the word before
+  int cnt = 0;
+  // groups of eight entries of T, the next group in flight while this one is used (two buffers in turn)
+  struct Group {
+    double a[8], b[8];
+  };
+  auto load = [&](int i0, Group& G) __attribute__((always_inline)) {
 #pragma unroll
-  for (int m = 0; m < M; ++m) {
-    q[m] = sa[0] - x[m];
-    cnt[m] = q[m] < 0.0;
-  }
-#pragma unroll 4
-  for (int i = 1; i < N; ++i) {
-    const double ai = sa[i], bi = sb2[i - 1];
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-      q[m] = fma(-bi, __builtin_amdgcn_rcp(q[m]), ai - x[m]);
-      cnt[m] += q[m] < 0.0;
+    for (int j = 0; j < 8; ++j) {
+      G.a[j] = sa[i0 + j];
+      G.b[j] = sb2[i0 + j];  // b_{i-1}^2 (entry 0 multiplies p_{-1} = 0)
     }
+    __builtin_amdgcn_sched_barrier(0);  // keeps the loads ahead of the steps they overlap
+  };
+  auto steps = [&](const Group& G) __attribute__((always_inline)) {
+    const int e0 = (int)(__builtin_bit_cast(uint64_t, p0) >> 52) & 0x7ff;
+    const int e1 = (int)(__builtin_bit_cast(uint64_t, p1) >> 52) & 0x7ff;
+    const int e = 1023 - max(e0, e1);
+    p0 = __builtin_amdgcn_ldexp(p0, e);
+    p1 = __builtin_amdgcn_ldexp(p1, e);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const double p2 = fma(G.a[j] - x, p1, -(G.b[j] * p0));
+      sg = __builtin_amdgcn_alignbit(sg, (uint32_t)(__builtin_bit_cast(uint64_t, p2) >> 32), 31);
+      p0 = p1;
+      p1 = p2;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  static_assert(N % 32 == 0, "whole words");
+  Group ga, gb;
+  load(0, ga);
+#pragma unroll 1
+  for (int w = 0; w < N; w += 32) {
+    load(w + 8, gb);
+    steps(ga);
+    load(w + 16, ga);
+    steps(gb);
+    load(w + 24, gb);
+    steps(ga);
+    load(w + 32 < N ? w + 32 : w, ga);
+    steps(gb);
+    cnt += __builtin_popcount(sg ^ __builtin_amdgcn_alignbit(last, sg, 1));
+    last = sg;
   }
+  return cnt;
 }
 
 // ---- Householder tridiagonalisation ----------------------------------------------------------------------------
 // Step k reflects x = row k beyond the diagonal (the matrix is symmetric) onto alpha e_1 with H_k = I - beta v v^T,
 // v = x - alpha e_1; with p = A22 v, K = (beta^2 / 2) v^T p and w = beta p - K v, A22 <- A22 - v w^T - w v^T.
-// The matrix lives in LDS as fp32 [N][N]; the rank-2 update is two fp32 fmas per entry (v and w rounded to fp32),
-// each wave's share of A22 v is an fp32 sum over its rows, and the rest (the shares' total p, K, w, the scalars,
-// the reflectors) is fp64.
 //
-// kTriWaves waves (one per SIMD) run the reduction with one workgroup barrier per step.  Lane l of every wave owns
-// the CPL = N / 64 consecutive columns CPL l ..; row R belongs to wave R mod kTriWaves.  The update of step k - 1 is
-// applied lazily: step k
-//   1. brings row k up to date in registers (every wave, from the same LDS row), forms the reflector (every wave
-//      the same scalars; wave 0 writes the reflector, alpha and the diagonal entry),
-//   2. sweeps the wave's rows R > k: applies the pending update to them and accumulates the wave's share of A22 v
-//      (fp32 fmas of the fp32 entries and the fp32 copy of v over the wave's rows; the shares are summed in fp64),
-//   3. after the barrier, sums the shares in a fixed order, so K and w, the next pending update, come out
-//      identical in every wave.
-// s_vw[R] = {v_R, w_R} of the pending update and v'_R of the current step; every wave writes the same values to
-// it, each before reading them (LDS operations of one wave complete in issue order; the fences below stop the
-// compiler from moving LDS accesses across the points where other lanes' values are read).  The shares are double
-// buffered by step parity: a wave writes step k + 1's share only after the barrier that follows every wave's reads
-// of step k - 1's.
+// The matrix lives in registers as 16 x 16 fp32 tiles in the accumulator layout of v_mfma_f32_16x16x4_f32: tile wave W
+// of the kTriWaves (one per SIMD) holds the tile columns W, W + kTriWaves, ..  The rank-2 update of a tile is one such
+// MFMA (K slots 0 and 1 carry {v, w} against {-w, -v}, the other two zeros), and a wave's columns of A22 v are four FMAs
+// per tile, so nothing of the matrix goes through LDS and no row scalar is broadcast to a wave.  Tiles whose rows or
+// columns have all been reduced drop out (the loop over 16-row blocks is unrolled, the inner one is not).  p, K, w, the
+// scalars and the reflectors are fp64, in one further wave, the chain wave, whose lanes own N / 64 columns each.
+//
+// Step k, with three workgroup barriers (the other waves of the workgroup only meet them):
+//   chain   brings row k up to date with the pending update of step k - 1, forms the reflector and writes v;      [1]
+//   tiles   multiply their tiles by v: a lane's share sums the four rows it holds of each tile (fp32); the shares of the
+//           four lane groups and row k + 1 (without step k's update) go to LDS;                                   [2]
+//   chain   sums the shares in a fixed order, forms K and w and writes {v, w};                                    [3]
+//   tiles   apply the update on the matrix cores, beside the chain's next reflector.
+// What bounds it is the serial chain of a step (two 64-lane fp64 sums, square root and reciprocal, three LDS round trips
+// and barriers).  With the chain computed by every tile wave instead (one barrier per step) the four waves of each of
+// the two units on a CU compete for the SIMDs with the same 200 instructions.  512 units of N = 128: 230 us with the
+// matrix in LDS (four waves sweeping its rows, the scalars broadcast from LDS), 152 us with register tiles and every
+// wave computing the chain, 122 us so; one unit of N = 64: 52, 39 and 35 us.
 constexpr int kTriWaves = 4;
 
 __device__ __forceinline__ void wave_lds_sync() {
@@ -207,45 +242,111 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Waves 0 .. kTriWaves - 1 of the workgroup; the other waves meet the same N - 2 barriers.  Writes s_a (the diagonal
-// of T), s_b[0 .. N - 2] (its off-diagonal), the reflectors (v of step k in refl[k N ..]) and their beta.
+// LDS of the reduction: s_op [4][N] (v, w, 0, 0 of the pending update), s_vn [N] (v of the current step), share [4][N],
+// s_row [N], the last diagonal entry.
 template <int N>
-__device__ __forceinline__ void tri_reduce(float* A, float4* s_vw, double* share, double* s_a, double* s_b,
-                                           double* refl, double* refl_beta, int lane, int wave) {
-  constexpr int CPL = N / kWave;
-  constexpr int W = kTriWaves;
-  if (wave >= W) {
-    for (int k = 0; k < N - 2; ++k) __syncthreads();
-    return;
+struct TriLds {
+  static constexpr int kOp = 0, kVn = 4 * N, kShare = 5 * N, kRow = 9 * N, kDiag = 10 * N, kFloats = 10 * N + 4;
+};
+
+// The tile waves.  A [N][LDA] holds the matrix (read once, before the first barrier).
+template <int N, int LDA>
+__device__ __forceinline__ void tri_tiles(const float* A, float* lds, int lane, int wave) {
+  constexpr int NT = N / 16, CW = NT / kTriWaves;
+  using Lay = TriLds<N>;
+  const int g = lane >> 4, n = lane & 15;
+  const float* op_a = lds + Lay::kOp + g * N + n;                     // K slot g of tile row 0
+  const float* op_b = lds + Lay::kOp + (g < 2 ? 1 - g : g) * N + n;   // K slots 0 and 1 exchanged
+  const float* vn = lds + Lay::kVn + 4 * g;
+  f32x4 T[NT][CW];
+#pragma unroll
+  for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+    for (int c = 0; c < CW; ++c)
+      T[ti][c] = *reinterpret_cast<const f32x4*>(&A[(16 * (wave + kTriWaves * c) + n) * LDA + 16 * ti + 4 * g]);
+#pragma unroll
+  for (int b = 0; b < NT; ++b) {
+#pragma unroll 1
+    for (int k = 16 * b; k < (16 * b + 16 < N - 2 ? 16 * b + 16 : N - 2); ++k) {
+      __syncthreads();  // [1]
+      float pc[CW][4];
+#pragma unroll
+      for (int c = 0; c < CW; ++c) pc[c][0] = pc[c][1] = pc[c][2] = pc[c][3] = 0.0f;
+#pragma unroll
+      for (int ti = b; ti < NT; ++ti) {
+        const f32x4 vr = *reinterpret_cast<const f32x4*>(vn + 16 * ti);
+#pragma unroll
+        for (int c = 0; c < CW; ++c)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) pc[c][i] = fmaf(T[ti][c][i], vr[i], pc[c][i]);
+      }
+      const int k1 = k + 1, i1 = k1 & 3, g1 = (k1 >> 2) & 3;
+      const bool next_block = (k1 & 15) == 0;  // row k + 1 is in the next block's tiles
+#pragma unroll
+      for (int c = 0; c < CW; ++c) {
+        const int col = 16 * (wave + kTriWaves * c) + n;
+        lds[Lay::kShare + g * N + col] = (pc[c][0] + pc[c][1]) + (pc[c][2] + pc[c][3]);
+        f32x4 t = T[b][c];
+        if (b + 1 < NT && next_block) t = T[b + 1 < NT ? b + 1 : b][c];
+        const float rv = i1 & 2 ? (i1 & 1 ? t[3] : t[2]) : (i1 & 1 ? t[1] : t[0]);
+        if (g == g1) lds[Lay::kRow + col] = rv;
+      }
+      // the last diagonal entry rides along with the last step's row
+      if (b == NT - 1 && k == N - 3 && wave == kTriWaves - 1 && lane == kWave - 1)
+        lds[Lay::kDiag] = T[NT - 1][CW - 1][3];
+      __syncthreads();  // [2]
+      __syncthreads();  // [3]
+      // the update (tile columns left of block b are done; rows likewise)
+#pragma unroll
+      for (int c = 0; c < CW; ++c) {
+        const int tj = wave + kTriWaves * c;
+        if (tj >= b) {  // uniform over the wave
+          const float ob = -op_b[16 * tj];
+#pragma unroll
+          for (int ti = b; ti < NT; ++ti)
+            T[ti][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(op_a[16 * ti], ob, T[ti][c], 0, 0, 0);
+        }
+      }
+    }
   }
-  float vpf[CPL], wpf[CPL];  // pending update of the lane's columns (fp32, as applied)
+}
+
+// The chain wave.  Writes s_a (the diagonal of T), s_b[0 .. N - 2] (its off-diagonal), the reflectors (v of step k at
+// refl[k N ..], zero up to k) and their beta.
+template <int N>
+__device__ __forceinline__ void tri_chain(const float* A, float* lds, double* s_a, double* s_b, float* refl,
+                                          float* refl_beta, int lane) {
+  constexpr int CPL = N / kWave;
+  using Lay = TriLds<N>;
+  float vpf[CPL], wpf[CPL];  // pending update of the lane's columns CPL lane .. (fp32, as applied)
+  float ak[CPL];             // row k without the pending update
 #pragma unroll
   for (int c = 0; c < CPL; ++c) {
     vpf[c] = wpf[c] = 0.0f;
-    *reinterpret_cast<float2*>(&s_vw[CPL * lane + c]) = make_float2(0.0f, 0.0f);
-  }
-  auto upd = [&](float a, const float4& vw, int c) { return fmaf(-vw.x, wpf[c], fmaf(-vw.y, vpf[c], a)); };
-  // row k as the sweep of step k - 1 left it (loaded right after that step's barrier) and its pending-update
-  // scalars {v_k, w_k} (taken from the lane that holds column k, not through LDS)
-  float ak[CPL];
-  float4 vwk = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    ak[c] = A[CPL * lane + c];
 #pragma unroll
-  for (int c = 0; c < CPL; ++c) ak[c] = A[CPL * lane + c];
+    for (int q = 2; q < 4; ++q) lds[Lay::kOp + q * N + CPL * lane + c] = 0.0f;
+  }
+  float vk = 0.0f, wk = 0.0f;  // entries k of the pending v and w
+  __builtin_amdgcn_s_setprio(3);  // the tile waves wait for this one
+#pragma unroll 1
   for (int k = 0; k < N - 2; ++k) {
     const int k1 = k + 1;
-    // 1. row k under the pending update; its entries beyond the diagonal are x
-    double x[CPL];
-    double ss = 0.0;
+    // row k under the pending update; its entries beyond the diagonal are x
+    double x[CPL], ss = 0.0;
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
       const int C = CPL * lane + c;
-      const float a = upd(ak[c], vwk, c);
-      if (wave == 0 && C == k) s_a[k] = (double)a;
+      const float a = fmaf(-vk, wpf[c], fmaf(-wk, vpf[c], ak[c]));
+      if (C == k) s_a[k] = (double)a;
       x[c] = C > k ? (double)a : 0.0;
       ss += x[c] * x[c];
     }
     ss = wave_sum(ss);
-    const double x0 = lane_value(x[k1 % CPL], k1 / CPL);
+    double x0s = x[0];
+#pragma unroll
+    for (int c = 1; c < CPL; ++c) x0s = k1 % CPL == c ? x[c] : x0s;
+    const double x0 = lane_value(x0s, k1 / CPL);
     double ab[3];
     reflector_scalars(x0, ss, ab);
     const double beta = ab[2];
@@ -254,142 +355,99 @@ __device__ __forceinline__ void tri_reduce(float* A, float4* s_vw, double* share
     for (int c = 0; c < CPL; ++c) {
       const int C = CPL * lane + c;
       v[c] = C > k1 ? x[c] : (C == k1 ? ab[1] : 0.0);
-      s_vw[C].z = (float)v[c];
+      vpf[c] = (float)v[c];
+      lds[Lay::kVn + C] = vpf[c];
     }
-    if (wave == 0) {
-      double* refl_k = refl + __builtin_amdgcn_readfirstlane(k * N);
+    __syncthreads();  // [1]
+    float* refl_k = refl + __builtin_amdgcn_readfirstlane(k * N);
 #pragma unroll
-      for (int c = 0; c < CPL; ++c)
-        if (CPL * lane + c >= k1) refl_k[CPL * lane + c - k1] = v[c];
-      if (lane == 0) {
-        s_b[k] = ab[0];
-        refl_beta[k] = beta;
-      }
+    for (int c = 0; c < CPL; ++c) {
+      refl_k[CPL * lane + c] = vpf[c];
+      lds[Lay::kOp + CPL * lane + c] = vpf[c];
     }
-    wave_lds_sync();
-    // 2. the wave's rows R > k: the pending update, then p += a v'_R
-    float pf[CPL];
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) pf[c] = 0.0f;
-    const int R0 = k1 + ((wave - k1) % W + W) % W;  // first row > k of this wave
-    int R = R0;
-    for (; R + 3 * W < N; R += 4 * W) {
-      float4 vw[4];
-      float a[4][CPL];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        vw[j] = s_vw[R + j * W];
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) a[j][c] = A[(R + j * W) * N + CPL * lane + c];
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) {
-          a[j][c] = upd(a[j][c], vw[j], c);
-          A[(R + j * W) * N + CPL * lane + c] = a[j][c];
-          pf[c] = fmaf(a[j][c], vw[j].z, pf[c]);
-        }
+    if (lane == 0) {
+      s_b[k] = ab[0];
+      refl_beta[k] = (float)beta;
     }
-    if (R < N) {
-      // the last 1 - 3 rows, loaded together (a missing row re-reads row R and is neither stored nor counted)
-      const int m = (N - 1 - R) / W + 1;
-      float4 vw[3];
-      float a[3][CPL];
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        const int Rj = j < m ? R + j * W : R;
-        vw[j] = s_vw[Rj];
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) a[j][c] = A[Rj * N + CPL * lane + c];
-      }
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        if (j < m) {
-#pragma unroll
-          for (int c = 0; c < CPL; ++c) {
-            a[j][c] = upd(a[j][c], vw[j], c);
-            A[(R + j * W) * N + CPL * lane + c] = a[j][c];
-            pf[c] = fmaf(a[j][c], vw[j].z, pf[c]);
-          }
-        }
-      }
-    }
-    double* sh = share + (k & 1) * W * N;
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) sh[wave * N + CPL * lane + c] = (double)pf[c];
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) ak[c] = A[k1 * N + CPL * lane + c];
-    // 3. p = the sum of the shares; K = (beta^2 / 2) v^T p; w = beta p - K v becomes the pending update
+    const double hb = -0.5 * beta * beta;
+    __syncthreads();  // [2]
+    // p = the sum of the shares; K = (beta^2 / 2) v^T p; w = beta p - K v becomes the pending update
     double kk = 0.0, p[CPL];
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
-      double t = sh[CPL * lane + c];
-#pragma unroll
-      for (int w = 1; w < W; ++w) t += sh[w * N + CPL * lane + c];
-      p[c] = t;
-      kk += CPL * lane + c > k ? v[c] * t : 0.0;
+      const int C = CPL * lane + c;
+      ak[c] = lds[Lay::kRow + C];
+      const float* sh = lds + Lay::kShare + C;
+      p[c] = ((double)sh[0] + (double)sh[N]) + ((double)sh[2 * N] + (double)sh[3 * N]);
+      kk += C > k ? v[c] * p[c] : 0.0;
     }
-    const double K = 0.5 * beta * beta * wave_sum(kk);
+    const double K = hb * wave_sum(kk);
+    float vsel = 0.0f, wsel = 0.0f;
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
       const int C = CPL * lane + c;
-      vpf[c] = (float)v[c];
-      wpf[c] = C > k ? (float)(beta * p[c] - K * v[c]) : 0.0f;
-      *reinterpret_cast<float2*>(&s_vw[C]) = make_float2(vpf[c], wpf[c]);
+      wpf[c] = C > k ? (float)(beta * p[c] + K * v[c]) : 0.0f;
+      lds[Lay::kOp + N + C] = wpf[c];
+      vsel = c == 0 || k1 % CPL == c ? vpf[c] : vsel;
+      wsel = c == 0 || k1 % CPL == c ? wpf[c] : wsel;
     }
-    float vsel = vpf[0], wsel = wpf[0];
-#pragma unroll
-    for (int c = 1; c < CPL; ++c)
-      if (k1 % CPL == c) {
-        vsel = vpf[c];
-        wsel = wpf[c];
-      }
-    vwk.x = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, vsel), k1 / CPL));
-    vwk.y = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wsel), k1 / CPL));
+    vk = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, vsel), k1 / CPL));
+    wk = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wsel), k1 / CPL));
+    __syncthreads();  // [3]
   }
-  // the last pending update on the trailing 2 x 2 block
-  if (wave == 0) {
-    wave_lds_sync();
+  __builtin_amdgcn_s_setprio(0);
+  // the last pending update on the trailing 2 x 2 block: row N - 2 is in ak, entry (N - 1, N - 1) beside it
 #pragma unroll
-    for (int R = N - 2; R < N; ++R) {
-      const float4 vw = s_vw[R];
-#pragma unroll
-      for (int c = 0; c < CPL; ++c) {
-        const int C = CPL * lane + c;
-        const float a = upd(A[R * N + C], vw, c);
-        if (C == R) s_a[R] = (double)a;
-        if (R == N - 2 && C == N - 1) s_b[N - 2] = (double)a;
-      }
+  for (int c = 0; c < CPL; ++c) {
+    const int C = CPL * lane + c;
+    const float a = fmaf(-vk, wpf[c], fmaf(-wk, vpf[c], ak[c]));
+    if (C == N - 2) s_a[N - 2] = (double)a;
+    if (C == N - 1) {
+      s_b[N - 2] = (double)a;
+      s_a[N - 1] = (double)fmaf(-vpf[c], wpf[c], fmaf(-wpf[c], vpf[c], lds[Lay::kDiag]));
     }
   }
 }
 
-// LDS layout (bytes): the matrix region MREG holds, in turn, G / the trailing matrix as fp32 [N][N] (phases 1-2),
+template <int N, int LDA>
+__device__ __forceinline__ void tri_reduce(const float* A, float* lds, double* s_a, double* s_b, float* refl,
+                                           float* refl_beta, int lane, int wave, int side) {
+  const int chain = kTriWaves + side;
+  if (wave < kTriWaves) {
+    tri_tiles<N, LDA>(A, lds, lane, wave);
+  } else if (wave == chain) {
+    tri_chain<N>(A, lds, s_a, s_b, refl, refl_beta, lane);
+  } else {
+    for (int k = 0; k < 3 * (N - 2); ++k) __syncthreads();
+  }
+}
+
+// LDS layout (bytes): the matrix region MREG holds, in turn, G as fp32 [N][N + 4] (until the reduction has it in
+// registers; the padding spreads the 16 rows of a tile over the banks), the bisection's scaled T and counts (phase 3),
 // the inverse-iteration scratch fp64 [N][kInvBatch] x 2 (phase 4), X fp32 [r][N] (MGS, back-transformation); then
-// fp64 scalars and vectors; then the staging region: the sweep's per-wave shares of A22 v, fp64 [2][kTriWaves][N],
-// during phase 2, a chunk of reflectors during phase 5.  About 79 KB for N = 128, so two units share a CU.
+// fp64 scalars and vectors; then the staging region: the reduction's vectors during phase 2, a chunk of reflectors
+// during phase 5.  81024 bytes for N = 128, so two units share a CU.
 template <int N>
 struct EigLds {
-  static constexpr size_t kMat = (size_t)N * N * 4;
+  static constexpr int kLda = N + 4;
+  static constexpr size_t max2(size_t a, size_t b) { return a > b ? a : b; }
+  static constexpr size_t kMat = (size_t)N * kLda * 4;
   static constexpr size_t kScratch = (size_t)2 * N * kInvBatch * 8;
   static constexpr size_t kX = (size_t)KVC_MAX_RANK * N * 4;
-  static constexpr size_t kMreg = ((kMat > kScratch ? (kMat > kX ? kMat : kX) : (kScratch > kX ? kScratch : kX)) +
-                                   15) / 16 * 16;
-  // s_a, s_b [N]; s_lam [KVC_MAX_RANK]; s_misc [8]; s_vw float4 [N] (later b^2 [N])
-  static constexpr size_t kSmall = (size_t)(2 * N + KVC_MAX_RANK + 8) * 8 + (size_t)N * 16;
-  static constexpr size_t kShare = (size_t)2 * kTriWaves * N * 8;
+  static constexpr size_t kMreg = (max2(kMat, max2(kScratch, kX)) + 15) / 16 * 16;
+  // s_a, s_b [N]; s_lam [KVC_MAX_RANK]; s_misc [8]
+  static constexpr size_t kSmall = (size_t)(2 * N + KVC_MAX_RANK + 8) * 8;
+  static constexpr size_t kTri = (size_t)TriLds<N>::kFloats * 4;
   static constexpr size_t kReflStage = (size_t)kReflChunk * (N + 1) * 4;
-  static constexpr size_t kStage = kShare > kReflStage ? kShare : kReflStage;
+  static constexpr size_t kStage = max2(kTri, kReflStage);
   static constexpr size_t kTotal = kMreg + kSmall + kStage;
 };
 
-// Eight waves per SIMD (at most 64 VGPRs) so that two 1024-thread units share a CU.
+// Four waves per SIMD (at most 128 VGPRs) so that two 512-thread units share a CU.
 template <int N>
-__global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(8))) void eig_topr(EigArgs a) {
+__global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(4))) void eig_topr(EigArgs a) {
   using Lay = EigLds<N>;
-  constexpr int LD = N;
+  constexpr int LDA = Lay::kLda;
   extern __shared__ __attribute__((aligned(16))) double smem[];
   char* base = reinterpret_cast<char*>(smem);
   float* A = reinterpret_cast<float*>(base);             // G, then the trailing matrix (fp32 storage)
@@ -400,26 +458,34 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(8))
   double* s_b = s_a + N;                    // off-diagonal of T: b[i] couples i and i + 1
   double* s_lam = s_b + N;                  // eigenvalues, descending
   double* s_misc = s_lam + KVC_MAX_RANK;    // scalars
-  float4* s_vw = reinterpret_cast<float4*>(s_misc + 8);  // {v_C, w_C, v'_C, -} of the tridiagonalisation
-  double* s_b2 = reinterpret_cast<double*>(s_vw);        // b^2 (after the tridiagonalisation)
-  double* share = reinterpret_cast<double*>(base + Lay::kMreg + Lay::kSmall);  // shares of A22 v [2][W][N]
-  float* s_rb = reinterpret_cast<float*>(share);  // reflector chunk fp32 [kReflChunk][N] (back-transformation)
+  double* s_as = reinterpret_cast<double*>(base);        // bisection: the scaled diagonal [N] and b^2 [N], then counts
+  double* s_b2 = s_as + N;
+  float* s_tri = reinterpret_cast<float*>(base + Lay::kMreg + Lay::kSmall);  // vectors of the reduction (TriLds)
+  float* s_rb = s_tri;                            // reflector chunk fp32 [kReflChunk][N] (back-transformation)
   float* s_rbeta = s_rb + kReflChunk * N;
 
   const int u = blockIdx.x;
+  // Phases that keep one or two waves busy start from wave 1 in every second round of 256 units (one round over the
+  // CUs): waves are dealt to the SIMDs in turn, the second unit of a CU one SIMD on from the first (read back on 512
+  // units), so the two units then use different SIMDs.
+  const int side = (u >> 8) & 1;
   if (a.skip && a.skip[u]) return;  // whole workgroup
   const UnitTarget tg = eig_target(a, u);
   const int r = tg.rank;
   if (r <= 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  double* refl = a.reflect + (size_t)u * N * N;          // v_k in row k
-  double* refl_beta = a.reflect_beta + (size_t)u * N;
-  double* gvec = a.vecs + (size_t)u * N * KVC_MAX_RANK;  // eigenvectors of T, vector j in row j
+  float* refl = reinterpret_cast<float*>(a.reflect + (size_t)u * N * N);  // v_k in row k, fp32
+  float* refl_beta = reinterpret_cast<float*>(a.reflect_beta + (size_t)u * N);
+  float* gvec = reinterpret_cast<float*>(a.vecs + (size_t)u * N * KVC_MAX_RANK);  // eigenvectors of T in rows, fp32
 
   // ---- 1. load G ------------------------------------------------------------------------------------------
   // Each thread takes Q groups of 4 consecutive entries; every load of a partial (or of the dense matrix) is issued
   // before its values are added, and the partials are added in order c = 0, 1, ... in fp64.
-  static_assert(LD == N && (N * N) % (4 * kEigThreads) == 0, "whole float4 groups per thread");
+  static_assert((N * N) % (4 * kEigThreads) == 0, "whole float4 groups per thread");
+  auto place = [&](int q) {  // thread's q-th group of four entries in the padded matrix
+    const int e = 4 * (tid + q * kEigThreads);
+    return reinterpret_cast<float4*>(A + (e / N) * LDA + e % N);
+  };
   constexpr int Q = N * N / (4 * kEigThreads);
   if (a.partials) {
     const int parts = (tg.tokens + a.part_tokens - 1) / a.part_tokens;
@@ -427,7 +493,7 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(8))
     double acc[Q][4];
 #pragma unroll
     for (int q = 0; q < Q; ++q) acc[q][0] = acc[q][1] = acc[q][2] = acc[q][3] = 0.0;
-#pragma unroll 2
+#pragma unroll 1
     for (int c = 0; c < parts; ++c) {
       float4 v[Q];
 #pragma unroll
@@ -442,7 +508,7 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(8))
     }
 #pragma unroll
     for (int q = 0; q < Q; ++q)
-      reinterpret_cast<float4*>(A)[tid + q * kEigThreads] =
+      *place(q) =
           make_float4((float)acc[q][0], (float)acc[q][1], (float)acc[q][2], (float)acc[q][3]);
   } else {
     const double2* D2 = reinterpret_cast<const double2*>(a.dense + (size_t)u * N * N);
@@ -454,15 +520,14 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(8))
     }
 #pragma unroll
     for (int q = 0; q < Q; ++q)
-      reinterpret_cast<float4*>(A)[tid + q * kEigThreads] =
+      *place(q) =
           make_float4((float)v[2 * q].x, (float)v[2 * q].y, (float)v[2 * q + 1].x, (float)v[2 * q + 1].y);
   }
   __syncthreads();
 
   // ---- 2. Householder tridiagonalisation ------------------------------------------------------------------------
-  tri_reduce<N>(A, s_vw, share, s_a, s_b, refl, refl_beta, lane, wave);
+  tri_reduce<N, LDA>(A, s_tri, s_a, s_b, refl, refl_beta, lane, wave, side);
   __syncthreads();
-  for (int i = tid; i < N - 1; i += kEigThreads) s_b2[i] = fmax(s_b[i] * s_b[i], 2.2250738585072014e-308);
   if (wave == 0) {
     // Gershgorin interval of T (minima and maxima: any order gives the same result)
     double lo = s_a[0], hi = s_a[0];
@@ -493,89 +558,80 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(8))
     __syncthreads();
   } else {
     // ---- 3. multisection bisection for the r largest eigenvalues ---------------------------------------
+    // everything scaled by a power of two that brings the norm of T into [1, 2)
+    const int sexp = 1023 - ((int)(__builtin_bit_cast(uint64_t, tnorm) >> 52) & 0x7ff);
+    for (int i = tid; i < N; i += kEigThreads) {
+      s_as[i] = __builtin_amdgcn_ldexp(s_a[i], sexp);
+      const double bs = i > 0 ? __builtin_amdgcn_ldexp(s_b[i - 1], sexp) : 0.0;
+      s_b2[i] = fmax(bs * bs, 7.52316384526264e-37);  // b_{i-1}^2, floored at 2^-120
+    }
+    __syncthreads();
     {
       int rp = 1;
       while (rp < r) rp <<= 1;
-      // P lanes per eigenvalue, each evaluating kBisShifts shifts: the bracket is cut into S = P kBisShifts + 1
-      // pieces per step
-      constexpr int P = 8;
-      static_assert(kEigThreads / KVC_MAX_RANK >= P, "P lanes for every eigenvalue");
-      constexpr int S = P * kBisShifts + 1;
-      // (tid passes through an empty asm so that the compiler does not keep tid / P live until the
-      // back-transformation, which takes the same quotient, and spill it)
-      int tidb = tid;
+      // P lanes per eigenvalue, one shift each: the bracket is cut into S = P + 1 pieces per step: many lanes (few steps) while two units leave each SIMD a wave at the most, four from rank 17 on
+      // (P x steps is the work, and there it fills the SIMDs)
+      const int plog = r <= 8 ? 5 : (r <= 16 ? 3 : 2), P = 1 << plog;
+      static_assert(kEigThreads / KVC_MAX_RANK >= 4, "four lanes for every eigenvalue");
+      const int S = P + 1;
+      // (through an empty asm so that the compiler does not keep the quotient live until the back-transformation, which
+      // takes a similar one, and spill it)
+      int tidb = (tid + kEigThreads - kWave * side) & (kEigThreads - 1);
       asm volatile("" : "+v"(tidb));
-      const int grp = tidb / P, s = tidb - grp * P;
+      const int grp = tidb >> plog, s = tidb - (grp << plog);
       const int kasc = N - 1 - grp;                  // ascending index of the target eigenvalue
-      double lo = s_misc[1], hi = s_misc[2];
-      // First step, shared by all targets: the rp P lanes cut the Gershgorin interval at M = rp P kBisShifts
+      double lo = __builtin_amdgcn_ldexp(s_misc[1], sexp), hi = __builtin_amdgcn_ldexp(s_misc[2], sexp);
+      // First step, shared by all targets: M lanes (at least one per SIMD lane) cut the Gershgorin interval at M
       // points (counts to LDS, in the matrix region, free since the reduction); each target's lanes then count
       // the cut points left of it, so every bracket starts at 1 / (M + 1) of the interval.
-      const int M = rp * P * kBisShifts;
-      int* s_cnt = reinterpret_cast<int*>(A);
-      if (tid < rp * P) {
-        double x[kBisShifts];
-        int c[kBisShifts];
-#pragma unroll
-        for (int m = 0; m < kBisShifts; ++m) {
-          x[m] = lo + (hi - lo) * (double)(tid * kBisShifts + m + 1) / (double)(M + 1);
-          c[m] = 0;
-        }
-        sturm_counts<N, kBisShifts>(s_a, s_b2, x, c);
-#pragma unroll
-        for (int m = 0; m < kBisShifts; ++m) s_cnt[tid * kBisShifts + m] = c[m];
+      const int M = max(rp * P, 256);
+      int* s_cnt = reinterpret_cast<int*>(s_b2 + N);
+      if (tidb < M) {
+        const double x = lo + (hi - lo) * (double)(tidb + 1) / (double)(M + 1);
+        s_cnt[tidb] = sturm_count<N>(s_as, s_b2, x);
       }
       __syncthreads();
       if (grp < rp) {
         // counts do not decrease along the cut points, so those left of the target are a prefix; lane s scans
         // the s-th of P equal slices
-        const int per = M / P;  // rp kBisShifts, even
+        const int per = M / P;
         int left = 0;
-#pragma unroll 4
-        for (int j = s * per; j < (s + 1) * per; j += 2) {
-          const int2 c2 = *reinterpret_cast<const int2*>(&s_cnt[j]);
-          left += (c2.x <= kasc) + (c2.y <= kasc);
-        }
-        left = sum8i(left);
+#pragma unroll 8
+        for (int j = s * per; j < (s + 1) * per; ++j) left += s_cnt[j] <= kasc;
+        left += dpp32i<kDppXor1>(left);
+        left += dpp32i<kDppXor2>(left);
+        if (P > 4) left += dpp32i<kDppHalfMirror>(left);
+        for (int o = 8; o < P; o <<= 1) left += __shfl_xor(left, o, kWave);
         const double nlo = left == 0 ? lo : lo + (hi - lo) * (double)left / (double)(M + 1);
         const double nhi = left == M ? hi : lo + (hi - lo) * (double)(left + 1) / (double)(M + 1);
         lo = nlo;
         hi = nhi;
       }
-      // then S-way steps per target until the bracket is below 2^-25 of the Gershgorin interval, the accuracy of
-      // the counts themselves
+      // then S-way steps per target until the bracket is below 2^-28 of the Gershgorin interval: finer than the
+      // rounding of the fp32 matrix the reduction worked on, so that eigenvalues which only that rounding separates
+      // still get shifts of their own, and inverse iteration vectors that are far from parallel
       int iters = 0;
-      for (double w = (double)(M + 1); w < 33554432.0; w *= S) ++iters;
+      for (double w = (double)(M + 1); w < 268435456.0; w *= S) ++iters;
       for (int it = 0; it < iters; ++it) {
-        double x[kBisShifts];
-        int c[kBisShifts];
-#pragma unroll
-        for (int m = 0; m < kBisShifts; ++m) {
-          x[m] = lo + (hi - lo) * (double)(s * kBisShifts + m + 1) / (double)S;
-          c[m] = 0;
-        }
-        if (grp < r) sturm_counts<N, kBisShifts>(s_a, s_b2, x, c);
+        const double x = lo + (hi - lo) * (double)(s + 1) / (double)S;
+        const int c = grp < r ? sturm_count<N>(s_as, s_b2, x) : 0;
         // shifts left of the target form a prefix of the S - 1 cut points; sstar counts them
-        int sstar = 0;
-#pragma unroll
-        for (int m = 0; m < kBisShifts; ++m) {
-          const uint64_t mask = __ballot(c[m] <= kasc);
-          sstar += __popcll((mask >> ((lane / P) * P)) & ((1ull << P) - 1ull));
-        }
+        const uint64_t mask = __ballot(c <= kasc);
+        const int sstar = __popcll((mask >> (lane & ~(P - 1))) & ((1ull << P) - 1ull));
         const double nlo = sstar == 0 ? lo : lo + (hi - lo) * (double)sstar / (double)S;
         const double nhi = sstar == S - 1 ? hi : lo + (hi - lo) * (double)(sstar + 1) / (double)S;
         lo = nlo;
         hi = nhi;
       }
-      if (grp < r && s == 0) s_lam[grp] = 0.5 * (lo + hi);
+      if (grp < r && s == 0) s_lam[grp] = __builtin_amdgcn_ldexp(0.5 * (lo + hi), -sexp);
     }
     __syncthreads();
 
     // ---- 4. inverse iteration, kInvBatch vectors per batch, one lane each ------------------------------
     const double piv = 2.220446049250313e-16 * tnorm;
     for (int j0 = 0; j0 < r; j0 += kInvBatch) {
-      const int j = j0 + tid;
-      if (tid < kInvBatch && j < r) {
+      const int jl = lane, j = j0 + jl;
+      if (wave == side && jl < kInvBatch && j < r) {
         const double lam = s_lam[j];
         // LDL^T of T - lam I without pivoting (tiny pivots replaced): invd[i] = 1 / d_i, in one pass with the
         // pseudo-random start x and the first solve's forward substitution z_i = x_i - b_{i-1} z_{i-1} / d_{i-1}
@@ -599,11 +655,11 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(8))
               const uint32_t h = hash3(a.seed ^ (uint32_t)u, (uint32_t)j, (uint32_t)i);
               const double x0 = (double)(h >> 11) * (1.0 / 2097152.0) - 1.0;
               z = i > 0 ? x0 - bv[t] * id * z : x0;
-              xv[i * kInvBatch + tid] = z;
+              xv[i * kInvBatch + jl] = z;
               double d = i > 0 ? (av[t] - lam) - bv[t] * id * bv[t] : av[t] - lam;
               if (fabs(d) < piv) d = copysign(piv, d);
               id = recip(d);
-              invd[i * kInvBatch + tid] = id;
+              invd[i * kInvBatch + jl] = id;
             }
           }
         }
@@ -617,14 +673,14 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(8))
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
               const int i = i0 + t, im = i > 0 ? i - 1 : 0;
-              xw[t] = xv[i * kInvBatch + tid];
+              xw[t] = xv[i * kInvBatch + jl];
               bw[t] = s_b[im];
-              iw[t] = invd[im * kInvBatch + tid];
+              iw[t] = invd[im * kInvBatch + jl];
             }
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
               z = i0 + t > 0 ? xw[t] * sc - bw[t] * iw[t] * z : xw[t] * sc;
-              xv[(i0 + t) * kInvBatch + tid] = z;
+              xv[(i0 + t) * kInvBatch + jl] = z;
             }
           }
           double x = 0.0, mx = 0.0;
@@ -633,14 +689,14 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(8))
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
               const int i = i1 - t;
-              xw[t] = xv[i * kInvBatch + tid];
+              xw[t] = xv[i * kInvBatch + jl];
               bw[t] = s_b[i < N - 1 ? i : 0];
-              iw[t] = invd[i * kInvBatch + tid];
+              iw[t] = invd[i * kInvBatch + jl];
             }
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
               x = i1 - t == N - 1 ? xw[t] * iw[t] : (xw[t] - bw[t] * x) * iw[t];
-              xv[(i1 - t) * kInvBatch + tid] = x;
+              xv[(i1 - t) * kInvBatch + jl] = x;
               mx = fmax(mx, fabs(x));
             }
           }
@@ -649,17 +705,17 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(8))
         double ss = 0.0;
 #pragma unroll 4
         for (int i = 0; i < N; ++i) {
-          const double y = xv[i * kInvBatch + tid] * sc;
+          const double y = xv[i * kInvBatch + jl] * sc;
           ss += y * y;
         }
         const double f = sc / sqrt(ss);
 #pragma unroll 4
-        for (int i = 0; i < N; ++i) gvec[(size_t)j * N + i] = xv[i * kInvBatch + tid] * f;
+        for (int i = 0; i < N; ++i) gvec[(size_t)j * N + i] = (float)(xv[i * kInvBatch + jl] * f);
       }
       __syncthreads();
     }
     // X[j][i] in LDS (fp32 storage, fp64 arithmetic below)
-    for (int e = tid; e < r * N; e += kEigThreads) X[e] = (float)gvec[e];
+    for (int e = tid; e < r * N; e += kEigThreads) X[e] = gvec[e];
     __syncthreads();
 
     // modified Gram-Schmidt within clusters, one barrier per vector that has a later cluster member: the wave that
@@ -722,8 +778,10 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(8))
   // registers.  Reflectors are staged kReflChunk at a time at their absolute positions (zero up to k), so the steps
   // inside a chunk need no barrier.
   constexpr int PB = N / 8;
-  const int jv = tid >> 3, sub = tid & 7;
-  const bool wave_act = wave * (kWave / 8) < r;  // uniform
+  constexpr int kVecs = kEigThreads / 8;  // vectors per pass
+  for (int j0 = 0; j0 < r; j0 += kVecs) {
+  const int jv = j0 + (tid >> 3), sub = tid & 7;
+  const bool wave_act = j0 + wave * (kWave / 8) < r;  // uniform
   float xr[PB];
   if (jv < r) {
 #pragma unroll
@@ -753,11 +811,11 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(8))
         if (e < nk * N) {
           const int c = e / N, pos = e - c * N;
           const int k = kc - c;
-          if (pos > k) v = (float)refl[k * N + pos - k - 1];
+          if (pos > k) v = refl[k * N + pos];
         }
         pre[q] = v;
       }
-      preb = tid < nk ? (float)refl_beta[kc - tid] : 0.0f;
+      preb = tid < nk ? refl_beta[kc - tid] : 0.0f;
     };
     fetch(N - 3);
     for (int kc = N - 3; kc >= 0; kc -= kReflChunk) {
@@ -817,6 +875,7 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(8))
             make_float4(sgn * xr[i], sgn * xr[i + 1], sgn * xr[i + 2], sgn * xr[i + 3]);
       if (sub == 0 && tg.sigma) tg.sigma[jv] = (float)sqrt(fmax(s_lam[jv], 0.0));
     }
+  }
   }
 }
 

@@ -531,7 +531,7 @@ __device__ __forceinline__ void gram_f32_place(float* m, const f32x4* acc, int g
 // registers, and the four sums are added in a fixed order through LDS (tile fragments, 16 bytes per lane), then the
 // full matrix leaves in whole rows.  The next batch's rows are in flight while this one is multiplied.  Bound by the
 // fp32 matrix rate for head_dim 128 (36 tiles of 32 cycles per 4 tokens and wave), by latency for a few hundred
-// tokens (4 heads x 64, 256 tokens, two layers: GRAM_NEW us against 70 us for fp32 FMAs on operands read from LDS, one
+// tokens (4 heads x 64, 256 tokens, two layers: 20 us against 70 us for fp32 FMAs on operands read from LDS, one
 // output entry per thread and two LDS reads per FMA).
 template <int D>
 struct GramF32 {
@@ -866,7 +866,7 @@ __global__ __launch_bounds__(W * kWave) void proj_bf16_mfma(FitArgs a, int tpw, 
 // holds, of the row of token n, the 16-byte segments 16 q + 4 g .. + 3, and takes the same features of the basis row
 // from LDS, so both operands come in 16-byte reads and step (q, e) multiplies element e of segment q.  A workgroup of
 // four waves stages the basis once for 64 tpw tokens, each wave's next tile in flight behind the current one.  Bound by
-// memory from a few thousand rows on, by latency below (2 layers x 4 heads x 64, 256 tokens, rank 8: PROJ_NEW us against
+// memory from a few thousand rows on, by latency below (2 layers x 4 heads x 64, 256 tokens, rank 8: 4.1 us against
 // 50 us for one thread per (token, rank) reading every row once per rank).
 constexpr int kProjF32MaxTiles = 4;  // 16-token tiles per wave where the launch fills the chip anyway
 
