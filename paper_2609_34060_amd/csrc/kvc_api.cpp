@@ -172,7 +172,7 @@ FitPlan plan_fit(const kvc_cache* c, const kvc_batch* b, int32_t lb, int32_t le)
   p.max_parts = (p.max_parts + 3) / 4 * 4;
   size_t off = 0;
   p.off_partials = off;
-  off = align256(off + p.units * p.max_parts * d * d * sizeof(float));
+  off = align256(off + p.units * p.max_parts * kvc::gram_partial_floats(c->head_dim) * sizeof(float));
   p.off_reflect = off;
   off = align256(off + p.units * d * d * sizeof(double));
   p.off_beta = off;

@@ -479,38 +479,52 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(4))
   float* gvec = reinterpret_cast<float*>(a.vecs + (size_t)u * N * KVC_MAX_RANK);  // eigenvectors of T in rows, fp32
 
   // ---- 1. load G ------------------------------------------------------------------------------------------
-  // Each thread takes Q groups of 4 consecutive entries; every load of a partial (or of the dense matrix) is issued
-  // before its values are added, and the partials are added in order c = 0, 1, ... in fp64.
-  static_assert((N * N) % (4 * kEigThreads) == 0, "whole float4 groups per thread");
-  auto place = [&](int q) {  // thread's q-th group of four entries in the padded matrix
-    const int e = 4 * (tid + q * kEigThreads);
-    return reinterpret_cast<float4*>(A + (e / N) * LDA + e % N);
-  };
-  constexpr int Q = N * N / (4 * kEigThreads);
-  if (a.partials) {
+  // Every load of a partial (or of the dense matrix) is issued before its values are added, and the partials are added
+  // in order c = 0, 1, ... in fp64.  A thread takes whole tile fragments of the partials (four entries of a column) and
+  // places them and their mirror; rows and columns then stand in tile order, position 16 f + m for feature FT m + f,
+  // which the output undoes.  (A tile on the diagonal holds both halves itself.)
+  constexpr int FT = N / 16;
+  const bool tiled = a.partials != nullptr;
+  if (tiled) {
+    constexpr int kSlots = gram_tiles(N) * kWave, Q = (kSlots + kEigThreads - 1) / kEigThreads;
     const int parts = (tg.tokens + a.part_tokens - 1) / a.part_tokens;
-    const float4* P4 = reinterpret_cast<const float4*>(a.partials + (size_t)u * a.max_parts * N * N);
+    const f32x4* P4 = reinterpret_cast<const f32x4*>(a.partials + (size_t)u * a.max_parts * gram_partial_floats(N));
     double acc[Q][4];
 #pragma unroll
     for (int q = 0; q < Q; ++q) acc[q][0] = acc[q][1] = acc[q][2] = acc[q][3] = 0.0;
-#pragma unroll 1
+#pragma unroll 2
     for (int c = 0; c < parts; ++c) {
-      float4 v[Q];
+      f32x4 v[Q];
 #pragma unroll
-      for (int q = 0; q < Q; ++q) v[q] = P4[(size_t)c * (N * N / 4) + tid + q * kEigThreads];
+      for (int q = 0; q < Q; ++q) v[q] = P4[(size_t)c * kSlots + min(tid + q * kEigThreads, kSlots - 1)];
 #pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        acc[q][0] += (double)v[q].x;
-        acc[q][1] += (double)v[q].y;
-        acc[q][2] += (double)v[q].z;
-        acc[q][3] += (double)v[q].w;
-      }
+      for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[q][i] += (double)v[q][i];
     }
 #pragma unroll
-    for (int q = 0; q < Q; ++q)
-      *place(q) =
-          make_float4((float)acc[q][0], (float)acc[q][1], (float)acc[q][2], (float)acc[q][3]);
+    for (int q = 0; q < Q; ++q) {
+      const int tile = wave + q * kEigWaves;  // uniform over the wave
+      if (tile >= gram_tiles(N)) break;
+      int fi = 0, rem = tile;
+      while (rem >= FT - fi) {
+        rem -= FT - fi;
+        ++fi;
+      }
+      const int g4 = 16 * fi + 4 * (lane >> 4), n = 16 * (fi + rem) + (lane & 15);
+      const f32x4 v = {(float)acc[q][0], (float)acc[q][1], (float)acc[q][2], (float)acc[q][3]};
+      *reinterpret_cast<f32x4*>(A + n * LDA + g4) = v;
+      if (rem > 0)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) A[(g4 + i) * LDA + n] = v[i];
+    }
   } else {
+    static_assert((N * N) % (4 * kEigThreads) == 0, "whole groups of four entries per thread");
+    constexpr int Q = N * N / (4 * kEigThreads);
+    auto place = [&](int q) {  // thread's q-th group of four entries in the padded matrix
+      const int e = 4 * (tid + q * kEigThreads);
+      return reinterpret_cast<float4*>(A + (e / N) * LDA + e % N);
+    };
     const double2* D2 = reinterpret_cast<const double2*>(a.dense + (size_t)u * N * N);
     double2 v[2 * Q];
 #pragma unroll
@@ -862,17 +876,26 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(4))
     for (int i = 0; i < PB; ++i) mx = fmaxf(mx, fabsf(xr[i]));
     mx = max8(mx);
     const float thr = (float)((double)mx * (1.0 - 9.5367431640625e-07));
-    int key = 2 * N;  // 2 * position + sign bit of the first entry at or above the threshold
+    // feature of position sub PB + i: FT m + f for position 16 f + m (tile order), increasing with i either way
+    const int f0 = tiled ? FT * ((sub * PB) & 15) + (sub * PB >> 4) : sub * PB, fs = tiled ? FT : 1;
+    static_assert(PB == 8 || PB == 16, "a lane's positions lie in one tile row");
+    int key = 2 * N;  // 2 * feature + sign bit of the first entry at or above the threshold
 #pragma unroll
     for (int i = PB - 1; i >= 0; --i)
-      if (fabsf(xr[i]) >= thr) key = 2 * (sub * PB + i) + (xr[i] < 0.0f ? 1 : 0);
+      if (fabsf(xr[i]) >= thr) key = 2 * (f0 + fs * i) + (xr[i] < 0.0f ? 1 : 0);
     key = min8(key);
     const float sgn = (key < 2 * N && (key & 1)) ? -1.0f : 1.0f;
     if (jv < r) {
+      float* out = tg.basis + (size_t)jv * N + f0;
+      if (tiled) {  // the eight lanes of a vector write neighbouring features
 #pragma unroll
-      for (int i = 0; i < PB; i += 4)
-        *reinterpret_cast<float4*>(&tg.basis[(size_t)jv * N + sub * PB + i]) =
-            make_float4(sgn * xr[i], sgn * xr[i + 1], sgn * xr[i + 2], sgn * xr[i + 3]);
+        for (int i = 0; i < PB; ++i) out[FT * i] = sgn * xr[i];
+      } else {
+#pragma unroll
+        for (int i = 0; i < PB; i += 4)
+          *reinterpret_cast<float4*>(out + i) =
+              make_float4(sgn * xr[i], sgn * xr[i + 1], sgn * xr[i + 2], sgn * xr[i + 3]);
+      }
       if (sub == 0 && tg.sigma) tg.sigma[jv] = (float)sqrt(fmax(s_lam[jv], 0.0));
     }
   }

@@ -8,7 +8,7 @@
 // hi/lo pair; every product is hi*hi + hi*lo + lo*hi on v_mfma_f32_16x16x32_bf16 with fp32 accumulation, about
 // 16 significant bits per operand.  The Gram keeps the token index in the MFMA K slot by a permuted feature order
 // (see GramSeg) so that its operands come straight from coalesced row loads; only tiles on or above the diagonal
-// are computed and each is stored with its mirror.  In the projection the rows are read straight into the MFMA
+// are computed and stored.  In the projection the rows are read straight into the MFMA
 // B-operand layout (16 contiguous bytes per lane), the basis hi/lo is staged in LDS.
 // float32 caches use the fp32 matrix instruction (v_mfma_f32_16x16x4_f32): fp32 products and sums.
 #include <utility>
@@ -70,30 +70,18 @@ __device__ __forceinline__ void gram_tile(f32x4* acc, const typename GramSeg<D /
     acc[Q] = mfma16x16x32(ah, bh, acc[Q]);
   }
 }
-template <int D, int W, int Q>
-__device__ __forceinline__ void gram_store(float* P, const f32x4* acc, int g, int n) {
-  constexpr int FT = D / 16;
-  constexpr int idx = W + Q * kFitWaves;
-  if constexpr (idx < GramShape<D>::NTILES) {
-    constexpr int fi = tile_fi(idx, FT), fj = tile_fj(idx, FT);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = FT * (4 * g + i) + fi, col = FT * n + fj;
-      P[row * D + col] = acc[Q][i];
-      P[col * D + row] = acc[Q][i];
-    }
-  }
-}
 // All tiles of the upper triangle for one wave: acc[idx] += Z_fi^T Z_fj (hi/lo products).
 template <int D, int... Is>
 __device__ __forceinline__ void gram_all_tiles(f32x4* acc, const typename GramSeg<D / 16>::T* sh,
                                                const typename GramSeg<D / 16>::T* sl, std::integer_sequence<int, Is...>) {
   (gram_tile<D, Is, 0>(acc + Is, sh, sl), ...);
 }
-template <int D, int... Is>
-__device__ __forceinline__ void gram_all_stores(float* P, const f32x4* acc, int g, int n,
-                                                std::integer_sequence<int, Is...>) {
-  (gram_store<D, Is, 0>(P, acc + Is, g, n), ...);
+// A wave's partial: its accumulator fragments as they stand, 1 KB of consecutive lanes per tile (whole rows with both
+// mirrors took 288 scattered 4-byte stores per lane for head_dim 128; 8B/4K: 395 -> 264 us, serving layer 1809 -> 1609 us).
+template <int D>
+__device__ __forceinline__ void gram_store_fragments(float* P, const f32x4* acc, int lane) {
+#pragma unroll
+  for (int q = 0; q < gram_tiles(D); ++q) reinterpret_cast<f32x4*>(P)[q * kWave + lane] = acc[q];
 }
 
 // bf16 Gram, one wave per partial: the wave streams its own token range 32 tokens at a time.  Lane (g, m) loads,
@@ -241,8 +229,7 @@ __global__ __launch_bounds__(kFitThreads) void gram_bf16_mfma(FitArgs a) {
     gram_all_tiles<D>(acc, zh, zl, std::make_integer_sequence<int, NT>{});
   }
   const int64_t lu = fit_linear_unit(a, f);
-  float* P = a.partials + ((size_t)lu * a.max_parts + part) * D * D;
-  gram_all_stores<D>(P, acc, g, n, std::make_integer_sequence<int, NT>{});
+  gram_store_fragments<D>(a.partials + ((size_t)lu * a.max_parts + part) * gram_partial_floats(D), acc, lane);
 }
 
 // bf16 Gram, head_dim 128, rows staged through LDS: the same wave-per-partial Gram, but the rows of the next two
@@ -487,8 +474,7 @@ __global__ __launch_bounds__(kFitThreads) void gram_bf16_ring(FitArgs a) {
   gram_all_tiles<D>(acc, zc_h, zc_l, std::make_integer_sequence<int, NT>{});
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): no LDS load outstanding when the wave ends
   const int64_t lu = fit_linear_unit(a, f);
-  float* P = a.partials + ((size_t)lu * a.max_parts + part) * D * D;
-  gram_all_stores<D>(P, acc, g, n, std::make_integer_sequence<int, NT>{});
+  gram_store_fragments<D>(a.partials + ((size_t)lu * a.max_parts + part) * gram_partial_floats(D), acc, lane);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -511,34 +497,16 @@ template <int D, int... Is>
 __device__ __forceinline__ void gram_f32_tiles(f32x4* acc, const float* z, std::integer_sequence<int, Is...>) {
   (gram_f32_tile<D, Is>(acc, z), ...);
 }
-// Tile idx and its mirror into the full matrix m [D][LDM] in LDS.
-template <int D, int LDM, int... Is>
-__device__ __forceinline__ void gram_f32_place(float* m, const f32x4* acc, int g, int n,
-                                               std::integer_sequence<int, Is...>) {
-  constexpr int FT = D / 16;
-  auto one = [&](int fi, int fj, const f32x4& v) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = FT * (4 * g + i) + fi, col = FT * n + fj;
-      m[row * LDM + col] = v[i];
-      m[col * LDM + row] = v[i];
-    }
-  };
-  (one(tile_fi(Is, FT), tile_fj(Is, FT), acc[Is]), ...);
-}
-
 // One workgroup per partial: its four waves take the range's token batches in turn, each with every upper tile in
-// registers, and the four sums are added in a fixed order through LDS (tile fragments, 16 bytes per lane), then the
-// full matrix leaves in whole rows.  The next batch's rows are in flight while this one is multiplied.  Bound by the
+// registers, and the four sums are added in a fixed order through LDS (tile fragments, 16 bytes per lane).  The next batch's rows are in flight while this one is multiplied.  Bound by the
 // fp32 matrix rate for head_dim 128 (36 tiles of 32 cycles per 4 tokens and wave), by latency for a few hundred
 // tokens (4 heads x 64, 256 tokens, two layers: 20 us against 70 us for fp32 FMAs on operands read from LDS, one
 // output entry per thread and two LDS reads per FMA).
 template <int D>
 struct GramF32 {
-  static constexpr int FT = D / 16, NT = FT * (FT + 1) / 2, LDM = D + 4;
+  static constexpr int FT = D / 16, NT = gram_tiles(D);
   static constexpr int SF = D == 64 ? 4 : 2;  // 4-token steps per batch: 32 registers of rows per side pair
-  static constexpr size_t kFrag = (size_t)2 * NT * kWave * 16, kMat = (size_t)D * LDM * 4;
-  static constexpr size_t kLds = kFrag > kMat ? kFrag : kMat;
+  static constexpr size_t kLds = (size_t)2 * NT * kWave * 16;
 };
 
 template <int D, bool ROPE>
@@ -657,16 +625,11 @@ __global__ __launch_bounds__(kFitThreads) void gram_f32_mfma(FitArgs a) {
     if (wave < h)
 #pragma unroll
       for (int q = 0; q < NT; ++q) acc[q] += frag[(wave * NT + q) * kWave + lane];
-    __syncthreads();
+    if (h > 1) __syncthreads();
   }
-  float* m = reinterpret_cast<float*>(gram_lds);
-  if (wave == 0) gram_f32_place<D, GF::LDM>(m, acc, g, n, std::make_integer_sequence<int, NT>{});
-  __syncthreads();
-  float* P = a.partials + ((size_t)fit_linear_unit(a, f) * a.max_parts + c) * D * D;
-  for (int e = tid; e < D * D / 4; e += kFitThreads) {
-    const int row = e / (D / 4), col = 4 * (e % (D / 4));
-    *reinterpret_cast<f32x4*>(P + row * D + col) = *reinterpret_cast<const f32x4*>(m + row * GF::LDM + col);
-  }
+  if (wave == 0)
+    gram_store_fragments<D>(
+        a.partials + ((size_t)fit_linear_unit(a, f) * a.max_parts + c) * gram_partial_floats(D), acc, lane);
 }
 
 // ---------------------------------------------------------------------------------------------------------------

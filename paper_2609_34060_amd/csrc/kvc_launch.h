@@ -45,6 +45,10 @@ hipError_t launch_apply(const ApplyArgs& a, kvc_dtype dtype, int max_rank, int m
                         hipStream_t stream);
 
 // Fit (kvc_fit.hip): Gram partials, then projection after the eigensolver.
+// A partial Gram is stored as the accumulator fragments of its upper tiles, [tile][lane] of four floats in the order of
+// tile_fi / tile_fj: lane (g, n) of tile (fi, fj) holds G[FT (4 g + i) + fi][FT n + fj], i < 4, FT = d / 16.
+constexpr int gram_tiles(int d) { return (d / 16) * (d / 16 + 1) / 2; }
+constexpr int gram_partial_floats(int d) { return gram_tiles(d) * 64 * 4; }
 struct FitArgs {
   PoolView pv;
   LayerPtrs layers;
@@ -55,7 +59,7 @@ struct FitArgs {
   int32_t layer_begin;
   int32_t num_layers;
   int32_t mode;                // kvc_fit_mode
-  float* partials;             // workspace [unit][max_parts][d][d]
+  float* partials;             // workspace [unit][max_parts][gram_partial_floats(d)]
   int32_t max_parts;
   int32_t part_tokens;
   int32_t kv_begin;            // the launch covers K/V sides kv_begin .. (grid y: one or both sides' heads)
@@ -108,7 +112,7 @@ hipError_t launch_layer_proj(const LayerFitArgs& a, kvc_dtype dtype, int max_tok
 struct EigArgs {
   int32_t n;                  // head_dim
   int32_t num_units;
-  const float* partials;      // fp32 partial Grams [unit][max_parts][n][n], or null
+  const float* partials;      // fp32 partial Grams [unit][max_parts][gram_partial_floats(n)], or null
   int32_t max_parts;
   int32_t part_tokens;        // tokens per partial: a unit with T_s rows has ceil(T_s / part_tokens) partials
   const double* dense;        // fp64 Grams [unit][n][n] when partials is null
