@@ -615,8 +615,9 @@ __device__ __forceinline__ int64_t lane_row_offset(const PoolView& pv, const Lan
 // Every chunk of unit `unit` into LDS: a thread takes (feature f, eight ranks of one chunk); the lanes of a wave
 // take 64 consecutive features, so each of the eight 4-byte loads is one coalesced 256-byte row segment.  A thread
 // always takes the same feature (kResThreads is a multiple of D).  ROPE with `rot`: each basis row is rotated like a
-// key row at position `pos` (B R(pos)^T), from the partner feature's values and one angle per thread.
-template <int D, bool ROPE = false>
+// key row at position `pos` (B R(pos)^T), from the partner feature's values and one angle per thread.  NEG: negated (the
+// distances accumulate -A B onto the source row).
+template <int D, bool NEG, bool ROPE = false>
 __device__ __forceinline__ void stage_stacked(const AnchorArgs& a, int64_t unit, uint16_t* s_hi, uint16_t* s_lo,
                                               bool rot = false, double pos = 0.0) {
   static_assert(kResThreads % D == 0, "one feature per thread");
@@ -651,7 +652,7 @@ __device__ __forceinline__ void stage_stacked(const AnchorArgs& a, int64_t unit,
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
       uint32_t hh, ll;
-      split_bf16x2(x[2 * p], x[2 * p + 1], hh, ll);
+      split_bf16x2(NEG ? -x[2 * p] : x[2 * p], NEG ? -x[2 * p + 1] : x[2 * p + 1], hh, ll);
       hi[p] = hh;
       lo[p] = ll;
     }
@@ -661,15 +662,60 @@ __device__ __forceinline__ void stage_stacked(const AnchorArgs& a, int64_t unit,
   }
 }
 
+// Coefficient chunks of a tile.  The kernels below hold one tile's chunks in registers and, as soon as a chunk's
+// products are issued, load the next tile's into the same registers, so a wave always has a whole tile of loads in
+// flight behind its arithmetic (before, a tile's loads were issued and waited for at once, or only after the previous
+// tile).  For that every load is unconditional (a branch around a load makes the compiler wait for more than it needs):
+// VEC (ranks multiples of 8, an anchor's coefficients of one unit within 4 GiB) reads clamped rows and ranks, whose
+// products meet zero basis rows or are masked where they would count, and chunks past the last one read it again.  Other
+// ranks take the guarded element loads.
+template <bool VEC>
+__device__ __forceinline__ u32x4 load_chunk(const AnchorArgs& a, int c, int64_t unit, int t, int t_end, int g) {
+  const int v = a.chunk_anchor[c], k0 = a.chunk_k0[c], r = a.rank[v];
+  const uint16_t* coef = static_cast<const uint16_t*>(a.coef[v]) + unit * (int64_t)a.tokens[v] * r + k0;
+  if (VEC) {
+    const uint32_t k = k0 + 8 * g < r ? 8 * g : 0;
+    return *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(coef) +
+                                           2 * ((uint32_t)min(t, t_end - 1) * (uint32_t)r + k));
+  }
+  return t < t_end ? load_coef8(coef - k0, r, t, k0 + 8 * g) : u32x4{0u, 0u, 0u, 0u};
+}
+
+// Source row segments of token t; an absent row reads another one and is zeroed where it is used (row_mask).
+template <int NQ>
+__device__ __forceinline__ void load_row_clamped(const uint16_t* pool, int64_t off, int g, u32x4* raw) {
+  const uint16_t* row = pool + (off >= 0 ? off : 0) + 8 * g;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) raw[q] = *reinterpret_cast<const u32x4*>(row + 32 * q);
+}
+template <int NQ>
+__device__ __forceinline__ void row_mask(bool ok, u32x4* raw) {
+  if (__builtin_amdgcn_ballot_w64(!ok) != 0) {  // uniform, rare
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) raw[q] = ok ? raw[q] : u32x4{0u, 0u, 0u, 0u};
+  }
+}
+template <int NQ>
+__device__ __forceinline__ void row_f32(const u32x4* raw, f32x4* x) {
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    x[2 * q] = f32x4{bf16_lo_to_f32(raw[q][0]), bf16_hi_to_f32(raw[q][0]), bf16_lo_to_f32(raw[q][1]),
+                     bf16_hi_to_f32(raw[q][1])};
+    x[2 * q + 1] = f32x4{bf16_lo_to_f32(raw[q][2]), bf16_hi_to_f32(raw[q][2]), bf16_lo_to_f32(raw[q][3]),
+                         bf16_hi_to_f32(raw[q][3])};
+  }
+}
+
 // Eq. 8 with every anchor resident: per 16-token tile the accumulator starts from the source rows in fp32 and
 // takes w_v[t] (A_v[t, chunk c] B_v[chunk c]) over all chunks (the bf16 coefficients are exact MFMA operands against
 // the basis hi/lo, two MFMAs per fragment, and the product is scaled by the token's weight in fp32), then one
 // rounding.
 // ROPE: keys of a rotary cache, C_dst = R(pd - ps) C_src + sum_v w_v A_v (B_v R(pd)^T) (bases staged rotated, the
 // source rotated in the accumulator; rows past T_s get the rotated source).
-template <int D, bool ROPE>
+// 32 layers x 8 heads x 4096 tokens, ten anchors of rank 32: 680 us before the rolling loads, 649 us with them.
+template <int D, bool ROPE, int NCM, bool VEC>
 __global__ __launch_bounds__(kResThreads) void apply_anchored_res_bf16(AnchorArgs a) {
-  constexpr int MT = D / 16, NQ = D / 32, NCM = kResMaxChunks;
+  constexpr int MT = D / 16, NQ = D / 32;
   extern __shared__ __attribute__((aligned(16))) unsigned char anchor_lds[];
   const int NC = a.num_chunks, kpt = 32 * NC;
   uint16_t* s_hi = reinterpret_cast<uint16_t*>(anchor_lds);
@@ -681,7 +727,8 @@ __global__ __launch_bounds__(kResThreads) void apply_anchored_res_bf16(AnchorArg
   const int T = a.num_tokens, Ts = a.num_weighted, V = a.num_anchors;
   const int t_begin = blockIdx.x * kResChunk;
   if (t_begin >= T) return;  // whole workgroup
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave, g = lane >> 4, n = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int lane = threadIdx.x % kWave, g = lane >> 4, n = lane & 15;
   const int64_t unit = unit_index(layer, kv, head, H);
   const uint16_t* src_pool = static_cast<const uint16_t*>(kv ? a.layers.v[lrel] : a.layers.k[lrel]);
   uint16_t* dst_pool = static_cast<uint16_t*>(const_cast<void*>(kv ? a.layers.v[lrel] : a.layers.k[lrel]));
@@ -691,63 +738,74 @@ __global__ __launch_bounds__(kResThreads) void apply_anchored_res_bf16(AnchorArg
   const bool shift = rope && a.dst_position != a.src_position;
   float tc = 1.0f, ts = 0.0f;  // this lane's entry of the wave's angle table for pd - ps
   if (shift) rope_wave_table<D>(a.pv.rope, (double)a.dst_position - (double)a.src_position, lane, tc, ts);
-  if (t_begin < Ts) {  // whole workgroup
-    stage_stacked<D, ROPE>(a, unit, s_hi, s_lo, rope, (double)a.dst_position);
-    __syncthreads();
-  }
   const int t_end = min(T, t_begin + kResChunk);
   const LaneTable lts = lane_table(a.pv, a.src_table, a.src_offset, t_begin, t_end, lane);
   const LaneTable ltd = lane_table(a.pv, a.dst_table, a.dst_offset, t_begin, t_end, lane);
+  const bool any = t_begin < Ts;  // uniform over the workgroup
+  // tiles of this wave: rows t0 + n, t0 = t_begin + (j kResWaves + wave) 16
+  const int nt = max(0, min(kResTiles, (t_end - t_begin - wave * 16 + kResWaves * 16 - 1) / (kResWaves * 16)));
+  auto tile_t0 = [&](int j) { return t_begin + (j * kResWaves + wave) * 16; };
 
-  struct Tile {
-    u32x4 raw[NQ];
-    u32x4 cw[NCM];
-    float w[NCM];
-    int64_t dof;
+  u32x4 raw[NQ], cw[NCM];
+  float w[NCM];
+  int64_t dof;
+  // the source row and the destination offset of tile j (a row whose source block id is out of range is neither read nor
+  // written); rows past the item read the last one and are not written
+  auto load_row = [&](int j) __attribute__((always_inline)) {
+    const int t = tile_t0(j) + n, tr = min(t, T - 1);
+    const int64_t so = lane_row_offset(a.pv, lts, a.src_table, a.src_offset, tr, true, head);
+    const int64_t d = lane_row_offset(a.pv, ltd, a.dst_table, a.dst_offset, tr, true, head);
+    load_row_clamped<NQ>(src_pool, so, g, raw);
+    dof = so >= 0 && t < T ? d : -1;
   };
-  auto load_tile = [&](int j, Tile& tl) __attribute__((always_inline)) {
-    const int t = t_begin + (j * kResWaves + wave) * 16 + n;
-    const bool valid = t < T, crow = t < Ts;
-    const int64_t so = lane_row_offset(a.pv, lts, a.src_table, a.src_offset, t, valid, head);
-    // a row whose source block id is out of range is neither read nor written
-    const int64_t dof = lane_row_offset(a.pv, ltd, a.dst_table, a.dst_offset, t, valid, head);
-    tl.dof = so >= 0 ? dof : -1;
-    load_row_segments<NQ>(src_pool, so, g, tl.raw);
+  auto load_c = [&](int j, int c) __attribute__((always_inline)) {
+    const int t = tile_t0(j) + n;
+    cw[c] = load_chunk<VEC>(a, c, unit, t, Ts, g);
+    w[c] = wrow[(int64_t)min(t, Ts - 1) * V + a.chunk_anchor[c]];  // rows past T_s take no correction (below)
+  };
+  if (nt > 0) load_row(0);
+  if (any) {
+    if (nt > 0)
 #pragma unroll
-    for (int c = 0; c < NCM; ++c) {
-      tl.cw[c] = u32x4{0u, 0u, 0u, 0u};
-      tl.w[c] = 0.0f;
-      if (c < NC && crow) {
-        const int v = a.chunk_anchor[c], r = a.rank[v];
-        const uint16_t* coef = static_cast<const uint16_t*>(a.coef[v]) + unit * (int64_t)a.tokens[v] * r;
-        tl.cw[c] = load_coef8(coef, r, t, a.chunk_k0[c] + 8 * g);
-        tl.w[c] = wrow[(int64_t)t * V + v];
-      }
+      for (int c = 0; c < NCM; ++c) load_c(0, c);
+    stage_stacked<D, false, ROPE>(a, unit, s_hi, s_lo, rope, (double)a.dst_position);
+    __syncthreads();
+  }
+  auto store_tile = [&](const u32x4* o, int64_t d) __attribute__((always_inline)) {
+    if (d >= 0) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) *reinterpret_cast<u32x4*>(dst_pool + d + 32 * q + 8 * g) = o[q];
     }
   };
-  // the corrected (or copied) rows of tile j, ready to store
-  auto finish_tile = [&](int j, const Tile& tl, u32x4* outw) __attribute__((always_inline)) {
-    const int t0 = t_begin + (j * kResWaves + wave) * 16, t = t0 + n;
-    if (t0 < Ts || shift) {  // uniform over the wave
-      f32x4 acc[MT];
+  auto pack = [&](const f32x4* acc, u32x4* o) __attribute__((always_inline)) {
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        acc[2 * q] = f32x4{bf16_lo_to_f32(tl.raw[q][0]), bf16_hi_to_f32(tl.raw[q][0]),
-                           bf16_lo_to_f32(tl.raw[q][1]), bf16_hi_to_f32(tl.raw[q][1])};
-        acc[2 * q + 1] = f32x4{bf16_lo_to_f32(tl.raw[q][2]), bf16_hi_to_f32(tl.raw[q][2]),
-                               bf16_lo_to_f32(tl.raw[q][3]), bf16_hi_to_f32(tl.raw[q][3])};
-      }
-      if (ROPE && shift) rope_rotate_rows_wave<D>(acc, style, g, tc, ts);
+    for (int q = 0; q < NQ; ++q) {
+      const f32x4 x = acc[2 * q], y = acc[2 * q + 1];
+      o[q] = u32x4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
+    }
+  };
+  int j = 0;
+  const int nc = any ? max(0, min(nt, (Ts - t_begin - wave * 16 + kResWaves * 16 - 1) / (kResWaves * 16))) : 0;
+#pragma unroll 1
+  for (; j < nc; ++j) {  // tiles with covered rows
+    const int t = tile_t0(j) + n, jn = min(j + 1, nt - 1);
+    const int64_t d = dof;
+    u32x4 keep[NQ], outw[NQ];
+    f32x4 acc[MT];
 #pragma unroll
-      for (int c = 0; c < NCM; ++c) {
-        if (t0 >= Ts) break;  // uniform: a tile past the coverage takes the rotated source only
-        if (c >= NC) break;
+    for (int q = 0; q < NQ; ++q) keep[q] = raw[q];
+    row_f32<NQ>(raw, acc);
+    if (ROPE && shift) rope_rotate_rows_wave<D>(acc, style, g, tc, ts);
+    load_row(jn);
+#pragma unroll
+    for (int c = 0; c < NCM; ++c) {
+      if (c < NC) {
         int kc = kpt;
         asm volatile("" : "+s"(kc));  // keeps the fragment reads in this chunk's step (not hoisted out of the tiles)
         // the chunk's reconstruction from the exact bf16 coefficients (basis hi/lo), then scaled by the lane's
         // token weight in fp32: lane (g, n) holds rows 4g .. 4g + 3 of token n's column
-        const bf16x8 cb = as_bf16x8(tl.cw[c]);
-        const float wc = tl.w[c];
+        const bf16x8 cb = as_bf16x8(cw[c]);
+        const float wc = t < Ts ? w[c] : 0.0f;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
           const int f = mfma_row_feature(mt, n);
@@ -758,48 +816,54 @@ __global__ __launch_bounds__(kResThreads) void apply_anchored_res_bf16(AnchorArg
           for (int e = 0; e < 4; ++e) acc[mt][e] = fmaf(wc, p[e], acc[mt][e]);
         }
       }
-      // rows past T_s have a zero correction: the rotated source with a shift, else bit copies
-      const bool crow = t < Ts || shift;
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        const f32x4 x = acc[2 * q], y = acc[2 * q + 1];
-        const u32x4 c = {pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(y[0], y[1]),
-                         pack_bf16x2(y[2], y[3])};
-        outw[q] = crow ? c : tl.raw[q];
+      load_c(jn, c);
+    }
+    if (tile_t0(j) + 16 > Ts) {  // uniform: the tile where the coverage ends
+      // rows past T_s: the rotated source with a shift, else bit copies
+      pack(acc, outw);
+      if (ROPE && shift) {
+        f32x4 src[MT];
+        row_f32<NQ>(keep, src);
+        rope_rotate_rows_wave<D>(src, style, g, tc, ts);
+        pack(src, keep);
       }
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) outw[q] = t < Ts ? outw[q] : keep[q];
+    } else {
+      pack(acc, outw);
+    }
+    store_tile(outw, d);
+  }
+#pragma unroll 1
+  for (; j < nt; ++j) {  // tiles past the coverage: the rotated source with a shift, else bit copies
+    const int64_t d = dof;
+    u32x4 outw[NQ];
+    if (ROPE && shift) {
+      f32x4 src[MT];
+      row_f32<NQ>(raw, src);
+      rope_rotate_rows_wave<D>(src, style, g, tc, ts);
+      pack(src, outw);
     } else {
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) outw[q] = tl.raw[q];
+      for (int q = 0; q < NQ; ++q) outw[q] = raw[q];
     }
-  };
-
-  // the next tile's loads are issued before this tile's stores, so waiting for them never waits for the stores
-  if (t_begin + wave * 16 >= T) return;  // whole wave
-  Tile cur;
-  load_tile(0, cur);
-  for (int j = 0; j < kResTiles; ++j) {
-    u32x4 outw[NQ];
-    finish_tile(j, cur, outw);
-    const int64_t dof = cur.dof;
-    const bool more = j + 1 < kResTiles && t_begin + ((j + 1) * kResWaves + wave) * 16 < T;  // uniform
-    if (more) load_tile(j + 1, cur);
-    if (dof >= 0) {
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) *reinterpret_cast<u32x4*>(dst_pool + dof + 32 * q + 8 * g) = outw[q];
-    }
-    if (!more) break;
+    load_row(min(j + 1, nt - 1));
+    store_tile(outw, d);
   }
 }
 
 // Distances with every anchor of one head resident: a workgroup covers 1024 tokens of one (layer, K/V) and walks
-// the heads, staging each head's anchors once.  Per tile and anchor the reconstruction A_v B_v accumulates over the
-// anchor's chunks (bf16 coefficients are exact MFMA operands, B as hi/lo), then |x - recon| (weights) or
-// (x - recon)^2 (gate) is summed over the row.  Lane (g, n) keeps the sums of anchors v = 4u + g of its tiles'
+// the heads, staging each head's anchors once.  Per tile and anchor the accumulator starts from the source row in fp32
+// and takes -A_v B_v over the anchor's chunks (bf16 coefficients are exact MFMA operands, B as hi/lo); then its magnitudes
+// (weights) or squares (gate) are summed over the row.  ONE: every anchor has one chunk (ranks up to 32), so the source
+// row itself is the first product's addend.  Lane (g, n) keeps the sums of anchors v = 4u + g of its tiles'
 // token n in registers across heads.
 // ROPE (weights): keys of a rotary cache are compared in canonical coordinates, R(-ps) C_src (the bases are canonical).
-template <int D, bool GATE, bool ROPE>
+// 32 layers x 8 heads x 4096 tokens, ten anchors of rank 32, before and with the rolling loads: weights 844 -> 648 us,
+// gate 470 -> 375 us; four anchors of rank 16: 509 -> 339 and 260 -> 177 us, apply 548 -> 324 us.
+template <int D, bool GATE, bool ROPE, int NCM, bool VEC, bool ONE>
 __global__ __launch_bounds__(kResThreads) void anchor_dist_res_bf16(AnchorArgs a) {
-  constexpr int MT = D / 16, NQ = D / 32, NCM = kResMaxChunks, TPW = GATE ? kResTiles : kResDistTiles;
+  constexpr int MT = D / 16, NQ = D / 32, TPW = GATE ? kResTiles : kResDistTiles;
   constexpr int CH = kResWaves * TPW * 16;  // tokens per workgroup
   static_assert(KVC_MAX_ANCHORS <= 16, "four anchors per lane group");
   extern __shared__ __attribute__((aligned(16))) unsigned char anchor_lds[];
@@ -816,7 +880,8 @@ __global__ __launch_bounds__(kResThreads) void anchor_dist_res_bf16(AnchorArgs a
   const int Tl = a.num_weighted;
   const int t_begin = blockIdx.x * CH;
   if (t_begin >= Tl) return;  // whole workgroup
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave, g = lane >> 4, n = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int lane = threadIdx.x % kWave, g = lane >> 4, n = lane & 15;
   const uint16_t* pool = static_cast<const uint16_t*>(kv ? a.layers.v[lrel] : a.layers.k[lrel]);
 
   // per-tile distances (the weights need each token's); the gate only needs their sum, so it keeps one set
@@ -831,101 +896,90 @@ __global__ __launch_bounds__(kResThreads) void anchor_dist_res_bf16(AnchorArgs a
   float tc = 1.0f, ts = 0.0f;  // this lane's entry of the wave's angle table for -ps
   if (rot) rope_wave_table<D>(a.pv.rope, -(double)a.src_position, lane, tc, ts);
   const LaneTable lts = lane_table(a.pv, a.src_table, a.src_offset, t_begin, min(Tl, t_begin + CH), lane);
+  const int nt = max(0, min(TPW, (Tl - t_begin - wave * 16 + kResWaves * 16 - 1) / (kResWaves * 16)));  // wave's tiles
+  auto tile_t0 = [&](int j) { return t_begin + (j * kResWaves + wave) * 16; };
 
-  struct Tile {
-    u32x4 raw[NQ];
-    u32x4 cw[NCM];
+  u32x4 raw[NQ], cw[NCM];
+  bool ok = false;  // the tile's row is present
+  auto load_row = [&](int j, int h) __attribute__((always_inline)) {
+    const int64_t off =
+        lane_row_offset(a.pv, lts, a.src_table, a.src_offset, min(tile_t0(j) + n, Tl - 1), true, h);
+    ok = off >= 0;
+    load_row_clamped<NQ>(pool, off, g, raw);
   };
+  // dist[0] always belongs to the current tile (the weights): the array is rotated by one after every tile (static
+  // register indices with a rolled tile loop), so after TPW tiles dist[j] is tile j's again
+  auto rotate_dist = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float d0 = dist[0][u];
+#pragma unroll
+      for (int jj = 0; jj + 1 < ND; ++jj) dist[jj][u] = dist[jj + 1][u];
+      dist[ND - 1][u] = d0;
+    }
+  };
+  if (nt > 0) {
+    const int64_t unit = unit_index(layer, kv, h_lo, H);
+    load_row(0, h_lo);
+#pragma unroll
+    for (int c = 0; c < NCM; ++c) cw[c] = load_chunk<VEC>(a, c, unit, tile_t0(0) + n, Tl, g);
+  }
   for (int h = h_lo; h < h_hi; ++h) {
-    const int64_t unit = unit_index(layer, kv, h, H);
     if (h > h_lo) __syncthreads();  // every wave is done with the previous head's bases
-    stage_stacked<D>(a, unit, s_hi, s_lo);
+    stage_stacked<D, true>(a, unit_index(layer, kv, h, H), s_hi, s_lo);
     __syncthreads();
-    auto load_tile = [&](int j, Tile& tl) __attribute__((always_inline)) {
-      const int t = t_begin + (j * kResWaves + wave) * 16 + n;
-      const bool valid = t < Tl;
-      load_row_segments<NQ>(pool, lane_row_offset(a.pv, lts, a.src_table, a.src_offset, t, valid, h), g, tl.raw);
+#pragma unroll 1
+    for (int j = 0; j < nt; ++j) {
+      // the tile after this one: the next of this head, then the first of the next head (at the end, this one again)
+      const bool last = j + 1 == nt;
+      const int hn = last && h + 1 < h_hi ? h + 1 : h, jn = !last ? j + 1 : (h + 1 < h_hi ? 0 : j);
+      const int64_t unit_n = unit_index(layer, kv, hn, H);
+      const bool valid = tile_t0(j) + n < Tl;
+      f32x4 xv[MT];  // the (canonical) source row in fp32
+      row_mask<NQ>(ok, raw);
+      row_f32<NQ>(raw, xv);
+      if (ROPE && rot) rope_rotate_rows_wave<D>(xv, style, g, tc, ts);
+      load_row(jn, hn);
+      f32x4 acc[MT];
 #pragma unroll
       for (int c = 0; c < NCM; ++c) {
-        tl.cw[c] = u32x4{0u, 0u, 0u, 0u};
-        if (c < NC && valid) {
-          const int v = a.chunk_anchor[c], r = a.rank[v];
-          const uint16_t* coef = static_cast<const uint16_t*>(a.coef[v]) + unit * (int64_t)a.tokens[v] * r;
-          tl.cw[c] = load_coef8(coef, r, t, a.chunk_k0[c] + 8 * g);
-        }
-      }
-    };
-    // dist[0] always belongs to the current tile (the weights): the array is rotated by one after every tile (static
-    // register indices with a rolled tile loop), so after TPW tiles dist[j] is tile j's again
-#pragma unroll 1
-    for (int j = 0; j < TPW; ++j) {
-      const int t0 = t_begin + (j * kResWaves + wave) * 16;
-      if (t0 < Tl) {  // uniform over the wave
-        Tile cur;
-        load_tile(j, cur);
-        const bool valid = t0 + n < Tl;
-        // ROPE: the canonical source rows R(-ps) C_src in fp32 (the rotary instantiation only)
-        f32x4 xv[ROPE ? MT : 1];
-        if constexpr (ROPE) {
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) {
-            xv[2 * q] = f32x4{bf16_lo_to_f32(cur.raw[q][0]), bf16_hi_to_f32(cur.raw[q][0]),
-                              bf16_lo_to_f32(cur.raw[q][1]), bf16_hi_to_f32(cur.raw[q][1])};
-            xv[2 * q + 1] = f32x4{bf16_lo_to_f32(cur.raw[q][2]), bf16_hi_to_f32(cur.raw[q][2]),
-                                  bf16_lo_to_f32(cur.raw[q][3]), bf16_hi_to_f32(cur.raw[q][3])};
-          }
-          if (rot) rope_rotate_rows_wave<D>(xv, style, g, tc, ts);
-        }
-        f32x4 acc[MT];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int c = 0; c < NCM; ++c) {
-          if (c < NC) {  // a guard, not a break: the loop must unroll fully (cw stays in registers)
+        if (c < NC) {
           int kc = kpt;
           asm volatile("" : "+s"(kc));  // keeps the fragment reads in this chunk's step
-          const bf16x8 cb = as_bf16x8(cur.cw[c]);
+          const bf16x8 cb = as_bf16x8(cw[c]);
+          if (!ONE && (c == 0 || a.chunk_last[c > 0 ? c - 1 : 0]))
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[mt] = xv[mt];
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt) {
             const int f = mfma_row_feature(mt, n);
-            acc[mt] = mfma16x16x32(res_frag(s_lo, kc, f, c, g), cb, acc[mt]);
+            acc[mt] = mfma16x16x32(res_frag(s_lo, kc, f, c, g), cb, ONE ? xv[mt] : acc[mt]);
             acc[mt] = mfma16x16x32(res_frag(s_hi, kc, f, c, g), cb, acc[mt]);
           }
-          if (a.chunk_last[c]) {  // uniform: anchor v's reconstruction is complete
-            float s = 0.0f;
+          if (ONE || a.chunk_last[c]) {  // uniform: anchor v's reconstruction is complete
+            float s0 = 0.0f, s1 = 0.0f;
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-#pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                const uint32_t w = cur.raw[q][e >> 1];
-                const float x = ROPE ? xv[ROPE ? 2 * q + (e >> 2) : 0][e & 3]
-                                     : ((e & 1) ? bf16_hi_to_f32(w) : bf16_lo_to_f32(w));
-                const float diff = x - acc[2 * q + (e >> 2)][e & 3];
-                s += GATE ? diff * diff : fabsf(diff);
-              }
+            for (int mt = 0; mt < MT; ++mt) {
+              s0 += GATE ? acc[mt][0] * acc[mt][0] : fabsf(acc[mt][0]);
+              s1 += GATE ? acc[mt][1] * acc[mt][1] : fabsf(acc[mt][1]);
+              s0 += GATE ? acc[mt][2] * acc[mt][2] : fabsf(acc[mt][2]);
+              s1 += GATE ? acc[mt][3] * acc[mt][3] : fabsf(acc[mt][3]);
             }
+            float s = s0 + s1;
             s += __shfl_xor(s, 16, kWave);
             s += __shfl_xor(s, 32, kWave);
             s = valid ? s : 0.0f;
             const int v = a.chunk_anchor[c];
 #pragma unroll
             for (int u = 0; u < 4; ++u) dist[0][u] += (v == 4 * u + g) ? s : 0.0f;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-          }
           }
         }
+        cw[c] = load_chunk<VEC>(a, c, unit_n, tile_t0(jn) + n, Tl, g);
       }
-      if constexpr (!GATE) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const float d0 = dist[0][u];
-#pragma unroll
-          for (int jj = 0; jj + 1 < TPW; ++jj) dist[jj][u] = dist[jj + 1][u];
-          dist[TPW - 1][u] = d0;
-        }
-      }
+      if constexpr (!GATE) rotate_dist();
     }
+    if constexpr (!GATE)
+      for (int j = nt; j < TPW; ++j) rotate_dist();
   }
   __syncthreads();  // the bases are no longer read: LDS now holds the per-token (or per-wave) sums
   float* s_d = reinterpret_cast<float*>(anchor_lds);
@@ -1011,6 +1065,11 @@ static bool plan_resident(AnchorArgs& a) {
     }
   }
   a.num_chunks = nc;
+  for (int c = nc; c < kResMaxChunks; ++c) {  // read again by kernels instantiated for more chunks
+    a.chunk_anchor[c] = a.chunk_anchor[nc - 1];
+    a.chunk_k0[c] = a.chunk_k0[nc - 1];
+    a.chunk_last[c] = 1;
+  }
   return (size_t)a.pv.head_dim * 32 * nc * 2 * sizeof(uint16_t) <= kResMaxLds;
 }
 
@@ -1021,6 +1080,44 @@ static size_t res_lds_bytes(const AnchorArgs& a, int which) {
                       : which == 2 ? (size_t)kResWaves * a.num_anchors * sizeof(float)
                                    : 0;
   return std::max(basis, sums);
+}
+
+// Whether every anchor's coefficients can be read as clamped 16-byte chunks with 32-bit offsets (load_chunk<true>).
+static bool res_vec(const AnchorArgs& a) {
+  for (int v = 0; v < a.num_anchors; ++v)
+    if (a.rank[v] % 8 != 0 || (uint64_t)a.tokens[v] * a.rank[v] * sizeof(uint16_t) > UINT32_MAX) return false;
+  return true;
+}
+
+// Chunk counts are rounded up to the instantiated 4, 7 and 10 (a padding chunk costs its loads, which hit the cache).
+template <int D, bool GATE, bool ROPE>
+static hipError_t launch_dist_res(const AnchorArgs& a, dim3 grid, size_t lds, hipStream_t stream) {
+  if (!res_vec(a))
+    return launch_with_lds(anchor_dist_res_bf16<D, GATE, ROPE, kResMaxChunks, false, false>, grid, lds, a, stream,
+                           kResThreads);
+  const int nc = a.num_chunks;
+  if (nc == a.num_anchors) {
+    if (nc <= 4)
+      return launch_with_lds(anchor_dist_res_bf16<D, GATE, ROPE, 4, true, true>, grid, lds, a, stream, kResThreads);
+    if (nc <= 7)
+      return launch_with_lds(anchor_dist_res_bf16<D, GATE, ROPE, 7, true, true>, grid, lds, a, stream, kResThreads);
+    return launch_with_lds(anchor_dist_res_bf16<D, GATE, ROPE, 10, true, true>, grid, lds, a, stream, kResThreads);
+  }
+  if (nc <= 4)
+    return launch_with_lds(anchor_dist_res_bf16<D, GATE, ROPE, 4, true, false>, grid, lds, a, stream, kResThreads);
+  if (nc <= 7)
+    return launch_with_lds(anchor_dist_res_bf16<D, GATE, ROPE, 7, true, false>, grid, lds, a, stream, kResThreads);
+  return launch_with_lds(anchor_dist_res_bf16<D, GATE, ROPE, 10, true, false>, grid, lds, a, stream, kResThreads);
+}
+
+template <int D, bool ROPE>
+static hipError_t launch_anchored_res(const AnchorArgs& a, dim3 grid, size_t lds, hipStream_t stream) {
+  if (!res_vec(a))
+    return launch_with_lds(apply_anchored_res_bf16<D, ROPE, kResMaxChunks, false>, grid, lds, a, stream, kResThreads);
+  const int nc = a.num_chunks;
+  if (nc <= 4) return launch_with_lds(apply_anchored_res_bf16<D, ROPE, 4, true>, grid, lds, a, stream, kResThreads);
+  if (nc <= 7) return launch_with_lds(apply_anchored_res_bf16<D, ROPE, 7, true>, grid, lds, a, stream, kResThreads);
+  return launch_with_lds(apply_anchored_res_bf16<D, ROPE, 10, true>, grid, lds, a, stream, kResThreads);
 }
 
 template <int D, bool GATE, bool ROPE>
@@ -1052,8 +1149,8 @@ static hipError_t launch_weights_variant(const AnchorArgs& a, kvc_dtype dtype, h
     if (plan_resident(r)) {
       dim3 grid((a.num_weighted + kResDistChunk - 1) / kResDistChunk, 2, a.num_layers);
       const size_t rl = res_lds_bytes(r, 0);
-      return D == 64 ? launch_with_lds(anchor_dist_res_bf16<64, false, ROPE>, grid, rl, r, stream, kResThreads)
-                     : launch_with_lds(anchor_dist_res_bf16<128, false, ROPE>, grid, rl, r, stream, kResThreads);
+      return D == 64 ? launch_dist_res<64, false, ROPE>(r, grid, rl, stream)
+                     : launch_dist_res<128, false, ROPE>(r, grid, rl, stream);
     }
     dim3 grid((a.num_weighted + kAnchorChunk - 1) / kAnchorChunk, 2, a.num_layers);
     return D == 64 ? launch_dist_bf16<64, false, ROPE>(a, grid, lds, stream)
@@ -1084,8 +1181,8 @@ hipError_t launch_gate_distances(const AnchorArgs& args, kvc_dtype dtype, hipStr
     grid.y = a.pv.num_kv_heads;
     a.gate_chunks = (int)(grid.x * grid.y);
     const size_t rl = res_lds_bytes(a, 2);
-    e = D == 64 ? launch_with_lds(anchor_dist_res_bf16<64, true, false>, grid, rl, a, stream, kResThreads)
-                : launch_with_lds(anchor_dist_res_bf16<128, true, false>, grid, rl, a, stream, kResThreads);
+    e = D == 64 ? launch_dist_res<64, true, false>(a, grid, rl, stream)
+                : launch_dist_res<128, true, false>(a, grid, rl, stream);
   } else if (dtype == KVC_BF16) {
     // one partial per (layer, 512-token chunk, KV head), as the workspace query sizes
     grid.y = a.pv.num_kv_heads;
@@ -1110,8 +1207,8 @@ static hipError_t launch_anchored_variant(const AnchorArgs& a, kvc_dtype dtype, 
     if (plan_resident(r)) {
       dim3 grid((a.num_tokens + kResChunk - 1) / kResChunk, 2 * a.pv.num_kv_heads, a.num_layers);
       const size_t rl = res_lds_bytes(r, 1);
-      return D == 64 ? launch_with_lds(apply_anchored_res_bf16<64, ROPE>, grid, rl, r, stream, kResThreads)
-                     : launch_with_lds(apply_anchored_res_bf16<128, ROPE>, grid, rl, r, stream, kResThreads);
+      return D == 64 ? launch_anchored_res<64, ROPE>(r, grid, rl, stream)
+                     : launch_anchored_res<128, ROPE>(r, grid, rl, stream);
     }
     dim3 grid((a.num_tokens + kAnchoredChunk - 1) / kAnchoredChunk, 2 * a.pv.num_kv_heads, a.num_layers);
     return D == 64 ? launch_anchored_bf16<64, ROPE>(a, grid, lds, stream)
