@@ -105,6 +105,18 @@ __device__ __forceinline__ void rope_table(const RopeView& rp, int D, double p, 
     s[i] = (float)sn;
   }
 }
+// Two tables at once (angles p0 and p1 per unit frequency), side by side on D threads.
+__device__ __forceinline__ void rope_tables2(const RopeView& rp, int D, double p0, float* c0, float* s0, double p1,
+                                             float* c1, float* s1) {
+  for (int i = threadIdx.x; i < D; i += blockDim.x) {
+    const bool second = i >= D / 2;
+    const int k = second ? i - D / 2 : i;
+    double sn, cs;
+    sincos((second ? p1 : p0) * rp.inv_freq[k], &sn, &cs);
+    (second ? c1 : c0)[k] = (float)cs;
+    (second ? s1 : s0)[k] = (float)sn;
+  }
+}
 __device__ __forceinline__ int rope_partner(int style, int D, int f) {
   return style == KVC_ROPE_HALF ? (f < D / 2 ? f + D / 2 : f - D / 2) : (f ^ 1);
 }
@@ -194,7 +206,7 @@ __device__ __forceinline__ void rope_rotate_rows_wave(f32x4* v, int style, int g
 // Offset of unit (layer, kv, head) in a state's per-unit arrays.
 // Position of a workgroup in a grid over (chunk, unit, item x layer) laid out by chunk_grid: order 0 has the chunks
 // fastest, 1 shifts each row's (y, z) chunks by the row index modulo the row length, 2 has the items fastest (x and
-// z trade places).
+// z trade places), each row's items shifted by the row index.
 __device__ __forceinline__ int grid_chunk(int order) {
   if (order == 2) return (int)blockIdx.z;
   if (order == 1) {
@@ -203,7 +215,11 @@ __device__ __forceinline__ int grid_chunk(int order) {
   }
   return (int)blockIdx.x;
 }
-__device__ __forceinline__ int grid_item_layer(int order) { return (int)(order == 2 ? blockIdx.x : blockIdx.z); }
+__device__ __forceinline__ int grid_item_layer(int order) {
+  if (order != 2) return (int)blockIdx.z;
+  const unsigned row = blockIdx.y + gridDim.y * blockIdx.z;
+  return (int)((blockIdx.x + row % gridDim.x) % gridDim.x);
+}
 
 __device__ __forceinline__ int64_t unit_index(int32_t layer, int32_t kv, int32_t head, int32_t num_kv_heads) {
   return ((int64_t)layer * 2 + kv) * num_kv_heads + head;

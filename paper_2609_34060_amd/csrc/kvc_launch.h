@@ -27,9 +27,11 @@ struct ApplyArgs {
 // chunks then idle while the others work.  Launches over several items therefore either rotate each row's chunk
 // order by the row index (kernels whose workgroups in a row share the unit's basis and tables, which then stay
 // next to one another), or put the items fastest (the Gram, whose few long partials per row gain most from
-// running every item's first partial first).  Measured on 64 requests of 1K-16K tokens at rank 64: projection
+// running every item's first partial first; each row shifts its items by one, since otherwise an item, and with it the
+// sum of a few lengths, always falls to the same XCD).  Measured on 64 requests of 1K-16K tokens at rank 64: projection
 // 2.07 -> 1.35 ms and apply 1.22 -> 1.19 ms rotated (1.93 and 1.70 ms with the items fastest); ring Gram 1.97 ->
-// 1.86 ms with the items fastest (2.0 ms rotated), and 2.15 -> 1.16 ms when the 64 lengths are equal.
+// 1.86 ms with the items fastest (2.0 ms rotated), and 2.15 -> 1.16 ms when the 64 lengths are equal; 1.61 -> 1.31 ms
+// with the items shifted per row and the ranges halved.
 constexpr int32_t kChunksFast = 0, kChunksRotated = 1, kItemsFast = 2;
 // The order a launch over num_items items with `chunks` chunks per row takes (the items-fast layout needs the
 // chunks within the z limit).
