@@ -19,6 +19,8 @@
 //
 // float32 caches: the same contraction on the fp32 matrix instruction (float32 throughout, for the 1e-5 storage
 // tolerance).
+#include <type_traits>
+
 #include "kvc_device.h"
 #include "kvc_launch.h"
 
@@ -28,7 +30,7 @@ constexpr int kApplyWaves = 4;
 constexpr int kApplyThreads = kApplyWaves * kWave;
 constexpr int kApplyF32Tiles = 4;                                       // float32 kernel: 16-token tiles per wave
 constexpr int kApplyChunkTokens = 256;                                  // bf16 kernel: tokens per workgroup
-constexpr int kApplyRopeChunkTokens = 1024;                             // the same with rotary keys
+constexpr int kApplyRopeChunkTokens = 1024, kApplyRopeFill = 2048;      // the same with rotary keys (see the launcher)
 
 // LDS of the bf16 kernel: basis hi/lo [D][KP] each, then the block-table slices of the workgroup's token chunk for
 // the source and the destination sequence (nblk entries each: a chunk of c tokens spans at most c / bs + 1 blocks).
@@ -104,8 +106,8 @@ __global__ __launch_bounds__(W * kWave) void apply_bf16_mfma(ApplyArgs a, int tp
   if (rope) {
     const int ps = itp->src_position, pd = itp->dst_position;
     shift = pd != ps;
-    rope_table(a.pv.rope, D, (double)pd - (double)ps, s_rope[0], s_rope[1]);
-    rope_table(a.pv.rope, D, (double)pd, s_rope[2], s_rope[3]);
+    rope_tables2(a.pv.rope, D, (double)pd - (double)ps, s_rope[0], s_rope[1], (double)pd, s_rope[2],
+                 s_rope[3]);
     __syncthreads();
   }
   if (correct) {
@@ -322,8 +324,8 @@ __global__ __launch_bounds__(kApplyThreads) void apply_f32_mfma(ApplyArgs a, int
   if (rope) {
     const int ps = itp->src_position, pd = itp->dst_position;
     shift = pd != ps;
-    rope_table(a.pv.rope, D, (double)pd - (double)ps, s_rope[0], s_rope[1]);
-    rope_table(a.pv.rope, D, (double)pd, s_rope[2], s_rope[3]);
+    rope_tables2(a.pv.rope, D, (double)pd - (double)ps, s_rope[0], s_rope[1], (double)pd, s_rope[2],
+                 s_rope[3]);
     __syncthreads();
   }
   if (correct) {
@@ -453,31 +455,32 @@ static hipError_t launch_bf16_w(const ApplyArgs& a, dim3 grid, int tpw, int nblk
 constexpr int apply_waves(int ks) { return ks == 1 ? 8 : 4; }
 
 // Keys of a rotary cache: every workgroup forms fp64 angle tables and stages a rotated basis, which a 1024-token chunk
-// (4 waves of 16 tiles) amortises; values (and every unit of a plain cache) take 256-token chunks.
+// (4 waves of 16 tiles) amortises; values (and every unit of a plain cache) take 256-token chunks in a launch of the
+// plain kernel, which runs more waves per SIMD.  While the keys alone leave the chip unfilled (below kApplyRopeFill
+// workgroups), with head_dim 128 and ranks up to 32, keys and values go in one launch of the rotary kernel in 512-token
+// chunks of 8 waves instead (two launches -> one: 28 layers x 4 heads x 3328 tokens, 448 key workgroups, 130 -> 112 us; 2
+// layers x 4 heads x 600 tokens 35 -> 20 us; 32 x 8 x 16384, 4096 of them, 992 -> 1093 us; rank 64 158 -> 160 us; head_dim
+// 64 63 -> 72 us).
 template <int D, int KS>
 static hipError_t launch_bf16(const ApplyArgs& a0, int max_tokens, int num_items, hipStream_t stream) {
   ApplyArgs a = a0;
-  const int H = a.pv.num_kv_heads;
-  int nkv = 2;
-  if (a.pv.rope.style != KVC_ROPE_NONE) {
-    const int chunk = kApplyRopeChunkTokens;
-    a.kv_begin = 0;
+  const int H = a.pv.num_kv_heads, il = num_items * a.num_layers;
+  auto launch = [&](auto rope, auto waves, int chunk, int kv_begin, int nkv) {
+    a.kv_begin = kv_begin;
     const int chunks = (max_tokens + chunk - 1) / chunk;
     a.chunk_order = multi_item_order(num_items, chunks, kChunksRotated);
-    const dim3 grid = chunk_grid(chunks, H, num_items * a.num_layers, a.chunk_order);
-    const hipError_t e = launch_bf16_w<D, KS, 4, true>(a, grid, chunk / 64,
-                                                       (chunk + a.pv.block_size - 1) / a.pv.block_size + 1, stream);
-    if (e != hipSuccess) return e;
-    a.kv_begin = 1;
-    nkv = 1;
-  }
-  const int chunk = kApplyChunkTokens;
-  constexpr int W = apply_waves(KS);
-  const int chunks = (max_tokens + chunk - 1) / chunk;
-  a.chunk_order = multi_item_order(num_items, chunks, kChunksRotated);
-  const dim3 grid = chunk_grid(chunks, nkv * H, num_items * a.num_layers, a.chunk_order);
-  return launch_bf16_w<D, KS, W, false>(a, grid, chunk / (16 * W), (chunk + a.pv.block_size - 1) / a.pv.block_size + 1,
-                                        stream);
+    return launch_bf16_w<D, KS, decltype(waves)::value, decltype(rope)::value>(
+        a, chunk_grid(chunks, nkv * H, il, a.chunk_order), chunk / (16 * decltype(waves)::value),
+        (chunk + a.pv.block_size - 1) / a.pv.block_size + 1, stream);
+  };
+  using Plain = std::integral_constant<int, apply_waves(KS)>;
+  if (a.pv.rope.style == KVC_ROPE_NONE) return launch(std::false_type{}, Plain{}, kApplyChunkTokens, 0, 2);
+  const int64_t key_groups = (int64_t)((max_tokens + kApplyRopeChunkTokens - 1) / kApplyRopeChunkTokens) * H * il;
+  if constexpr (KS == 1 && D == 128)
+    if (key_groups < kApplyRopeFill)
+      return launch(std::true_type{}, std::integral_constant<int, 8>{}, kApplyRopeChunkTokens / 2, 0, 2);
+  const hipError_t e = launch(std::true_type{}, std::integral_constant<int, 4>{}, kApplyRopeChunkTokens, 0, 1);
+  return e != hipSuccess ? e : launch(std::false_type{}, Plain{}, kApplyChunkTokens, 1, 1);
 }
 
 template <int D>

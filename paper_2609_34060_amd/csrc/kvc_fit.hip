@@ -109,8 +109,8 @@ __global__ __launch_bounds__(kFitThreads) void gram_bf16_mfma(FitArgs a) {
   const bool rope = ROPE && f.kv == 0;  // uniform over the workgroup
   const int style = a.pv.rope.style;
   if (rope) {
-    rope_table(a.pv.rope, D, -(double)itp->dst_position, s_rope[0], s_rope[1]);
-    rope_table(a.pv.rope, D, -(double)itp->src_position, s_rope[2], s_rope[3]);
+    rope_tables2(a.pv.rope, D, -(double)itp->dst_position, s_rope[0], s_rope[1], -(double)itp->src_position, s_rope[2],
+                 s_rope[3]);
     __syncthreads();
   }
   const int part = grid_chunk(a.chunk_order) * kFitWaves + wave;
@@ -535,8 +535,8 @@ __global__ __launch_bounds__(kFitThreads) void gram_f32_mfma(FitArgs a) {
   const int style = a.pv.rope.style;
   float rc[2][ROPE ? FT : 1], rsn[2][ROPE ? FT : 1];  // cos / sin of -pd and -ps for the lane's features
   if (rope) {
-    rope_table(a.pv.rope, D, -(double)itp->dst_position, s_rope[0], s_rope[1]);
-    rope_table(a.pv.rope, D, -(double)itp->src_position, s_rope[2], s_rope[3]);
+    rope_tables2(a.pv.rope, D, -(double)itp->dst_position, s_rope[0], s_rope[1], -(double)itp->src_position, s_rope[2],
+                 s_rope[3]);
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < (ROPE ? FT : 1); ++e) {
@@ -693,8 +693,8 @@ __global__ __launch_bounds__(W * kWave) void proj_bf16_mfma(FitArgs a, int tpw, 
   const bool rope = ROPE && f.kv == 0;  // uniform over the workgroup
   const int style = a.pv.rope.style;
   if (rope) {
-    rope_table(a.pv.rope, D, -(double)itp->dst_position, s_rope[0], s_rope[1]);
-    rope_table(a.pv.rope, D, -(double)itp->src_position, s_rope[2], s_rope[3]);
+    rope_tables2(a.pv.rope, D, -(double)itp->dst_position, s_rope[0], s_rope[1], -(double)itp->src_position, s_rope[2],
+                 s_rope[3]);
   }
   for (int e = tid; e < RP * D; e += W * kWave) {
     const int k = e / D;
@@ -876,8 +876,8 @@ __global__ __launch_bounds__(kFitThreads) void proj_f32_mfma(FitArgs a, int tpw)
   Rows cur;
   load_rows(0, cur);  // in flight while the basis is staged
   if (rope) {
-    rope_table(a.pv.rope, D, -(double)itp->dst_position, s_rope[0], s_rope[1]);
-    rope_table(a.pv.rope, D, -(double)itp->src_position, s_rope[2], s_rope[3]);
+    rope_tables2(a.pv.rope, D, -(double)itp->dst_position, s_rope[0], s_rope[1], -(double)itp->src_position, s_rope[2],
+                 s_rope[3]);
   }
   for (int e = tid; e < 16 * mtr * (D / 4); e += kFitThreads) {
     const int k = e / (D / 4), fe = 4 * (e % (D / 4));
