@@ -98,14 +98,22 @@ kvc_status check_batch(const kvc_cache* c, const kvc_batch* b, bool needs_src) {
   return KVC_OK;
 }
 
-// The kernels read the items from the caller's device scratch; the library writes the checked host items there on
-// the call's stream before its first launch, so no unchecked item reaches a kernel.
+// The kernels read the items of a batch from the caller's device scratch; the library writes the checked host items
+// there on the call's stream before its first launch, so no unchecked item reaches a kernel.  The item of a batch of one
+// travels in the kernel arguments instead (not in a per-layer fit, whose kernels run for milliseconds).
+bool in_arguments(const kvc_batch* b) { return b->num_items == 1; }
+
 kvc_status upload_items(const kvc_batch* b, hipStream_t stream) {
   const size_t bytes = static_cast<size_t>(b->num_items) * sizeof(kvc_item);
   return hip_status(hipMemcpyAsync(b->item_scratch, b->items, bytes, hipMemcpyHostToDevice, stream));
 }
 
-const kvc_item* device_items(const kvc_batch* b) { return static_cast<const kvc_item*>(b->item_scratch); }
+const kvc_item* scratch_items(const kvc_batch* b, int32_t first) {
+  return static_cast<const kvc_item*>(b->item_scratch) + first;
+}
+const kvc_item* device_items(const kvc_batch* b, int32_t first) {
+  return in_arguments(b) ? nullptr : scratch_items(b, first);
+}
 
 // With both tables NULL all items address the same identity-mapped rows: no destination range of the call may overlap
 // a source range or another destination range.  Sorted sweep over the row ranges of every item.
@@ -560,12 +568,11 @@ kvc_status kvc_apply(const kvc_cache* cache, const kvc_batch* batch, int32_t lay
   }
   if (!batch->src_tables && !batch->dst_tables && contiguous_ranges_overlap(batch)) return KVC_ERR_ALIAS;
   if (batch->num_items == 0 || layer_end == layer_begin || max_tokens == 0) return KVC_OK;
-  s = upload_items(batch, stream);
-  if (s != KVC_OK) return s;
+  if (!in_arguments(batch) && (s = upload_items(batch, stream)) != KVC_OK) return s;
   kvc::ApplyArgs a;
   std::memset(&a, 0, sizeof(a));
   fill_pool_view(cache, a.pv);
-  a.items = device_items(batch);
+  a.one = batch->items[0];
   a.src_tables = batch->src_tables;
   a.dst_tables = batch->dst_tables;
   a.max_blocks = batch->max_blocks;
@@ -582,7 +589,7 @@ kvc_status kvc_apply(const kvc_cache* cache, const kvc_batch* batch, int32_t lay
     for (int32_t i0 = 0; i0 < batch->num_items; i0 += per_launch_items) {
       const int32_t n = std::min(per_launch_items, batch->num_items - i0);
       kvc::ApplyArgs ai = a;
-      ai.items = device_items(batch) + i0;
+      ai.items = device_items(batch, i0);
       ai.src_tables = batch->src_tables ? batch->src_tables + static_cast<int64_t>(i0) * batch->max_blocks : nullptr;
       ai.dst_tables = batch->dst_tables ? batch->dst_tables + static_cast<int64_t>(i0) * batch->max_blocks : nullptr;
       s = hip_status(kvc::launch_apply(ai, cache->dtype, max_rank, max_tokens, n, stream));
@@ -637,7 +644,7 @@ kvc_status fit_per_layer(const kvc_cache* cache, const kvc_batch* batch, int32_t
     const kvc_state& st = batch->items[i].state;
     if (st.rank == 0 || st.num_tokens == 0) continue;
     la.rank = st.rank;
-    la.items = device_items(batch) + i;
+    la.items = scratch_items(batch, i);
     la.src_tables = batch->src_tables ? batch->src_tables + static_cast<int64_t>(i) * batch->max_blocks : nullptr;
     la.dst_tables = batch->dst_tables ? batch->dst_tables + static_cast<int64_t>(i) * batch->max_blocks : nullptr;
     for (int32_t l0 = layer_begin; l0 < layer_end; l0 += p.layers_per_group) {
@@ -707,13 +714,13 @@ kvc_status kvc_fit_state(const kvc_cache* cache, const kvc_batch* batch, int32_t
   const FitPlan p = plan_fit(cache, batch, layer_begin, layer_end);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) || workspace_bytes < p.total)
     return KVC_ERR_WORKSPACE;
-  s = upload_items(batch, stream);
-  if (s != KVC_OK) return s;
+  if (!in_arguments(batch) && (s = upload_items(batch, stream)) != KVC_OK) return s;
   char* ws = static_cast<char*>(workspace);
 
   kvc::FitArgs fa;
   std::memset(&fa, 0, sizeof(fa));
   fill_pool_view(cache, fa.pv);
+  fa.one = batch->items[0];
   fa.max_blocks = batch->max_blocks;
   fa.mode = mode;
   fa.partials = reinterpret_cast<float*>(ws + p.off_partials);
@@ -722,6 +729,7 @@ kvc_status kvc_fit_state(const kvc_cache* cache, const kvc_batch* batch, int32_t
   kvc::EigArgs ea;
   std::memset(&ea, 0, sizeof(ea));
   ea.n = cache->head_dim;
+  ea.state = batch->items[0].state;  // taken when the items are not on the device
   ea.partials = fa.partials;
   ea.max_parts = p.max_parts;
   ea.part_tokens = p.part_tokens;
@@ -740,7 +748,7 @@ kvc_status kvc_fit_state(const kvc_cache* cache, const kvc_batch* batch, int32_t
     }
     for (int32_t i0 = 0; i0 < batch->num_items; i0 += p.items_per_group) {
       const int32_t n = std::min(p.items_per_group, batch->num_items - i0);
-      fa.items = ea.items = device_items(batch) + i0;
+      fa.items = ea.items = device_items(batch, i0);
       fa.src_tables = batch->src_tables ? batch->src_tables + static_cast<int64_t>(i0) * batch->max_blocks : nullptr;
       fa.dst_tables = batch->dst_tables ? batch->dst_tables + static_cast<int64_t>(i0) * batch->max_blocks : nullptr;
       ea.num_units = n * fa.num_layers * 2 * cache->num_kv_heads;

@@ -60,7 +60,7 @@ __global__ __launch_bounds__(W * kWave) void apply_bf16_mfma(ApplyArgs a, int tp
   const int kv = a.kv_begin + (int)blockIdx.y / H;
   const int head = (int)blockIdx.y % H;
 
-  const kvc_item* itp = a.items + item_id;
+  const ItemPtr itp = item_ptr(a, item_id);
   const int T = itp->num_tokens;
   const int chunk = W * 16 * tpw;
   const int t_begin = grid_chunk(a.chunk_order) * chunk;
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(kApplyThreads) void apply_f32_mfma(ApplyArgs a, int
   const int kv = a.kv_begin + (int)blockIdx.y / H;
   const int head = (int)blockIdx.y % H;
 
-  const kvc_item* itp = a.items + item_id;
+  const ItemPtr itp = item_ptr(a, item_id);
   const int T = itp->num_tokens;
   const int chunk = kApplyWaves * 16 * tpw;
   const int t_begin = grid_chunk(a.chunk_order) * chunk;

@@ -100,7 +100,8 @@ __global__ __launch_bounds__(kFitThreads) void gram_bf16_mfma(FitArgs a) {
   constexpr int STEP = 32;
   using Seg = typename GramSeg<FT>::T;
   const FitUnit f = fit_unit(a);
-  const kvc_item* itp = a.items + f.item;
+  const kvc_item item = item_of(a, f.item);
+  const kvc_item* itp = &item;
   const int r = itp->state.rank;
   const int Ts = itp->state.num_tokens;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -298,7 +299,8 @@ __global__ __launch_bounds__(kFitThreads) void gram_bf16_ring(FitArgs a) {
   f.head = ((int)blockIdx.y % HG) * kFitWaves + wave;
   if (f.head >= H) return;
   f.unit = unit_index(f.layer, f.kv, f.head, H);
-  const kvc_item* itp = a.items + f.item;
+  const kvc_item item = item_of(a, f.item);
+  const kvc_item* itp = &item;
   const int r = itp->state.rank;
   const int Ts = itp->state.num_tokens;
   const int part = grid_chunk(a.chunk_order);
@@ -517,7 +519,8 @@ __global__ __launch_bounds__(kFitThreads) void gram_f32_mfma(FitArgs a) {
   __shared__ float s_rope[4][ROPE ? D / 2 : 1];  // cos / sin of -pd and -ps (rotary keys)
 
   const FitUnit f = fit_unit(a);
-  const kvc_item* itp = a.items + f.item;
+  const kvc_item item = item_of(a, f.item);
+  const kvc_item* itp = &item;
   const int r = itp->state.rank;
   const int Ts = itp->state.num_tokens;
   const int c = grid_chunk(a.chunk_order);
@@ -650,8 +653,9 @@ __host__ __device__ constexpr size_t proj_lds_bytes(int D, int RP, int nblk) {
   return (size_t)2 * RP * D * 2 + (size_t)2 * nblk * 4;
 }
 
+// (head_dim 64: six waves per SIMD, three workgroups of eight a CU)
 template <int D, int MTR, int W, bool ROPE>
-__global__ __launch_bounds__(W * kWave) void proj_bf16_mfma(FitArgs a, int tpw, int nblk) {
+__global__ __launch_bounds__(W * kWave, D == 64 && !ROPE && MTR <= 4 ? 6 : 1) void proj_bf16_mfma(FitArgs a, int tpw, int nblk) {
   constexpr int KS = D / 32;          // K-steps over features
   constexpr int RP = MTR * 16;        // padded rank
   extern __shared__ __attribute__((aligned(16))) uint16_t s_dyn[];
@@ -660,7 +664,8 @@ __global__ __launch_bounds__(W * kWave) void proj_bf16_mfma(FitArgs a, int tpw, 
   int32_t* s_tab = reinterpret_cast<int32_t*>(s_dyn + 2 * RP * D);  // [2][nblk]: source, destination
 
   const FitUnit f = fit_unit(a);
-  const kvc_item* itp = a.items + f.item;
+  const kvc_item item = item_of(a, f.item);
+  const kvc_item* itp = &item;
   const int r = itp->state.rank;
   const int Ts = itp->state.num_tokens;
   const int chunk = W * 16 * tpw;
@@ -839,7 +844,8 @@ __global__ __launch_bounds__(kFitThreads) void proj_f32_mfma(FitArgs a, int tpw)
   extern __shared__ __attribute__((aligned(16))) float s_b[];  // [16 mtr][LDB]
   __shared__ float s_rope[4][ROPE ? D / 2 : 1];                // cos / sin of -pd and -ps (rotary keys)
   const FitUnit f = fit_unit(a);
-  const kvc_item* itp = a.items + f.item;
+  const kvc_item item = item_of(a, f.item);
+  const kvc_item* itp = &item;
   const int r = itp->state.rank;
   const int Ts = itp->state.num_tokens;
   const int chunk = kFitWaves * 16 * tpw;

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 
 #include "kvc.h"
 #include "kvc_device.h"
@@ -11,7 +12,8 @@ namespace kvc {
 struct ApplyArgs {
   PoolView pv;
   LayerPtrs layers;            // pools of layers [layer_begin, layer_begin + num_layers)
-  const kvc_item* items;       // device
+  const kvc_item* items;       // device, or null: one item, `one`
+  kvc_item one;
   const int32_t* src_tables;   // device or null
   const int32_t* dst_tables;   // device or null
   int32_t max_blocks;
@@ -43,6 +45,24 @@ inline dim3 chunk_grid(int chunks, int units, int item_layers, int32_t order) {
   return order == kItemsFast ? dim3(item_layers, units, chunks) : dim3(chunks, units, item_layers);
 }
 
+// Item of a launch.  One item travels in the kernel arguments (no copy to the device ahead of the first kernel: that
+// copy and the gap after it cost about as much as a small apply).  item_ptr: Args is the kernel's first parameter, so
+// `one` lies at its own offset in the argument segment, and both places are read by scalar loads through one
+// constant-space pointer (a copy by value cost the apply of 64 requests 1-5 % in registers).  item_of: by value, for the
+// fit's kernels (with the constant-space pointer the compiler keeps the projection's LDS fragments in registers, 179
+// instead of 128).
+typedef const __attribute__((address_space(4))) kvc_item* ItemPtr;
+template <class Args>
+__device__ __forceinline__ ItemPtr item_ptr(const Args& a, int i) {
+  typedef const __attribute__((address_space(4))) char* Bytes;
+  return a.items ? (ItemPtr)(uintptr_t)(a.items + i)
+                 : (ItemPtr)((Bytes)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(Args, one));
+}
+template <class Args>
+__device__ __forceinline__ kvc_item item_of(const Args& a, int i) {
+  return a.items ? a.items[i] : a.one;
+}
+
 hipError_t launch_apply(const ApplyArgs& a, kvc_dtype dtype, int max_rank, int max_tokens, int num_items,
                         hipStream_t stream);
 
@@ -54,7 +74,8 @@ constexpr int gram_partial_floats(int d) { return gram_tiles(d) * 64 * 4; }
 struct FitArgs {
   PoolView pv;
   LayerPtrs layers;
-  const kvc_item* items;       // device; each item's state receives the fit
+  const kvc_item* items;       // device, or null: one item, `one`; each item's state receives the fit
+  kvc_item one;
   const int32_t* src_tables;
   const int32_t* dst_tables;
   int32_t max_blocks;

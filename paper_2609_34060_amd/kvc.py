@@ -7,9 +7,11 @@ fails loudly when the library has not been built.
 """
 from __future__ import annotations
 
+import collections
 import ctypes
 import os
-from typing import List, Optional, Sequence
+import threading
+from typing import Deque, Dict, List, Optional, Sequence, Tuple
 
 import torch
 
@@ -161,20 +163,34 @@ def _stream_handle(stream) -> ctypes.c_void_p:
     return ctypes.c_void_p(stream.cuda_stream)
 
 
-# The library copies a batch's host items (pinned memory) into its device scratch on the call's stream, so the copy
-# reads the host bytes only when the stream reaches it.  A Batch passed as a temporary would be freed on return and its
-# pinned block handed to the next allocation before that; calls that use the item scratch therefore keep their batch
-# alive until an event recorded after the call has completed.
-_inflight: list = []
+# The library copies the host items (pinned memory) of a batch of several into its device scratch on the call's stream,
+# so the copy reads the host bytes only when the stream reaches it, and the kernels read the batch's tables and states.  A
+# Batch passed as a temporary would be freed on return and its pinned block handed to the next allocation before that;
+# calls that use a batch's items therefore keep it alive until an event recorded after the call has completed.  A
+# stream's events complete in order, so each call looks at the oldest ones only (of every stream), and a completed event
+# serves again: a call that queried every event in flight and made a new one spent more host time the more were queued.
+_inflight: Dict[Tuple[int, int], Deque] = {}
+_inflight_lock = threading.Lock()
 
 
 def _hold_until_done(stream, batch: "Batch") -> None:
     if batch._host is None:
         return
-    ev = torch.cuda.Event()
-    ev.record(torch.cuda.current_stream() if stream is None else stream)
-    _inflight[:] = [x for x in _inflight if not x[0].query()]
-    _inflight.append((ev, batch))
+    st = torch.cuda.current_stream() if stream is None else stream
+    key = (st.device_index, st.cuda_stream)
+    with _inflight_lock:
+        free = None
+        for k in list(_inflight):
+            held = _inflight[k]
+            while held and held[0][0].query():
+                done = held.popleft()[0]
+                if k == key:
+                    free = done
+            if not held and k != key:
+                del _inflight[k]
+        ev = torch.cuda.Event() if free is None else free
+        ev.record(st)
+        _inflight.setdefault(key, collections.deque()).append((ev, batch))
 
 
 # ------------------------------------------------------------------------------------------------------------------
@@ -326,6 +342,7 @@ def kvc_dense_bytes(L: int, H: int, d: int, T: int, dtype: int) -> int:
 def kvc_apply(cache: Cache, batch: Batch, layer_begin: int = 0, layer_end: Optional[int] = None,
               stream=None) -> None:
     layer_end = cache.num_layers if layer_end is None else layer_end
+    stream = torch.cuda.current_stream() if stream is None else stream
     st = load().kvc_apply(ctypes.byref(cache.c), ctypes.byref(batch.b), layer_begin, layer_end,
                           _stream_handle(stream))
     _check(st, "kvc_apply")
@@ -340,8 +357,9 @@ def kvc_fit_workspace_bytes(cache: Cache, batch: Batch, layer_begin: int = 0, la
 def kvc_fit_state(cache: Cache, batch: Batch, layer_begin: int = 0, layer_end: Optional[int] = None,
                   mode: int = KVC_FIT_DELTA, workspace: Optional[torch.Tensor] = None, stream=None) -> None:
     layer_end = cache.num_layers if layer_end is None else layer_end
-    need = kvc_fit_workspace_bytes(cache, batch, layer_begin, layer_end)
-    if workspace is None:
+    stream = torch.cuda.current_stream() if stream is None else stream
+    if workspace is None:  # the call itself checks the size of a given one
+        need = kvc_fit_workspace_bytes(cache, batch, layer_begin, layer_end)
         workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=cache.k_pools[0].device)
     st = load().kvc_fit_state(ctypes.byref(cache.c), ctypes.byref(batch.b), layer_begin, layer_end, mode,
                               ctypes.c_void_p(workspace.data_ptr()), workspace.numel(), _stream_handle(stream))
@@ -359,8 +377,8 @@ def kvc_chain_workspace_bytes(first: State, second: State, out: State, layer_beg
 def kvc_chain(first: State, second: State, out: State, layer_begin: int = 0, layer_end: Optional[int] = None,
               workspace: Optional[torch.Tensor] = None, stream=None) -> None:
     layer_end = first.s.num_layers if layer_end is None else layer_end
-    need = kvc_chain_workspace_bytes(first, second, out, layer_begin, layer_end)
     if workspace is None:
+        need = kvc_chain_workspace_bytes(first, second, out, layer_begin, layer_end)
         workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=first.basis.device)
     st = load().kvc_chain(ctypes.byref(first.s), ctypes.byref(second.s), ctypes.byref(out.s), layer_begin,
                           layer_end, ctypes.c_void_p(workspace.data_ptr()), workspace.numel(),
@@ -423,8 +441,8 @@ def kvc_gate_distances(cache: Cache, batch: Batch, anchors: Anchors, prefix: int
     dev = cache.k_pools[0].device
     if distances is None:
         distances = torch.empty(len(anchors.states), dtype=torch.float32, device=dev)
-    need = kvc_gate_workspace_bytes(cache, anchors, prefix, layer_begin, layer_end)
     if workspace is None:
+        need = kvc_gate_workspace_bytes(cache, anchors, prefix, layer_begin, layer_end)
         workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
     st = load().kvc_gate_distances(ctypes.byref(cache.c), ctypes.byref(batch.b), ctypes.byref(anchors.a), prefix,
                                    layer_begin, layer_end, ctypes.c_void_p(distances.data_ptr()),
