@@ -1,0 +1,100 @@
+"""The dispatch rules between kernels of one call, on both sides of each line: the chunk counts and rank forms of the
+resident anchor kernels, and the item of a batch of one (kernel arguments) against the same item in a batch of two
+(device scratch).
+
+Anchors: bf16 rows and coefficients are exact operands and the basis carries 16 bits, so distances are within 1e-4 of
+fp64 (2^-17 of a reconstruction of RMS about 1, averaged), weights (softmax of -d at temperature 1) within 1e-3, and the
+corrected rows within the bf16 bar of 1e-2 of the slice's largest value."""
+import math
+
+import pytest
+import torch
+
+from paper_2609_34060_amd import kvc
+
+pytestmark = pytest.mark.gpu
+
+
+def _pools(L, H, d, bs, blocks, dtype, seed):
+    g = torch.Generator().manual_seed(seed)
+    return torch.randn(L, 2, blocks, bs, H, d, generator=g).to(dtype), torch.randperm(blocks, generator=g), g
+
+
+@pytest.mark.parametrize("d,ranks", [
+    (128, (32,)), (128, (32, 16, 8, 32)), (128, (8,) * 5), (128, (32,) * 7), (128, (24,) * 8), (64, (32,) * 10),
+    (128, (64, 32)), (128, (40, 96, 8)), (128, (64,) * 5), (128, (5, 32, 17)), (64, (33, 64, 1)), (128, (12,) * 9)])
+def test_resident_anchor_chunk_counts(d, ranks):
+    L, H, T, Ts, bs = 1, 2, 1201, 1187, 16
+    need = -(-(T + 5) // bs)
+    pool, ids, g = _pools(L, H, d, bs, 2 * need, torch.bfloat16, sum(ranks) + d)
+    tab = (ids[:need], ids[need:])
+    off, V = (3, 5), len(ranks)
+    rows = [(tab[i][(torch.arange(T) + off[i]) // bs], (torch.arange(T) + off[i]) % bs) for i in range(2)]
+    dev = pool.cuda()
+    cache = kvc.Cache([dev[l, 0] for l in range(L)], [dev[l, 1] for l in range(L)])
+
+    def states():
+        return [kvc.State((torch.randn(L, 2, H, Ts, r, generator=g)).to(torch.bfloat16).cuda(),
+                          (torch.randn(L, 2, H, r, d, generator=g) / math.sqrt(r)).cuda()) for r in ranks]
+
+    bases, deltas = states(), states()
+    empty = kvc.State(torch.zeros(L, 2, H, 0, 0, dtype=torch.bfloat16).cuda(), torch.zeros(L, 2, H, 0, d).cuda())
+    t = [x.to(torch.int32).view(1, -1).cuda() for x in tab]
+    batch = kvc.Batch([T], [off[0]], [off[1]], [empty], t[0], t[1])
+    an = kvc.Anchors(bases, Ts, L)
+    dist = kvc.kvc_gate_distances(cache, batch, an, Ts)
+    kvc.kvc_anchor_weights(cache, batch, an)
+    kvc.kvc_apply_anchored(cache, batch, an.with_states(deltas))
+    got = dev.cpu()
+
+    def recon(s, l, kv):
+        return torch.matmul(s.coef[l, kv].cpu().double(), s.basis[l, kv].cpu().double())  # [H, Ts, d]
+
+    square = torch.zeros(V, dtype=torch.float64)
+    for l in range(L):
+        for kv in range(2):
+            src = pool[l, kv][rows[0][0], rows[0][1]].double()  # [T, H, d]
+            offs = [src[:Ts].transpose(0, 1) - recon(s, l, kv) for s in bases]
+            dv = torch.stack([o.abs().mean(dim=(0, 2)) for o in offs], dim=-1)
+            w = torch.softmax(-dv, dim=-1)
+            assert (an.weights[l, kv].cpu().double() - w).abs().max() <= 1e-3
+            if kv == 1:
+                square += torch.stack([o.square().sum() for o in offs])
+            want = src.clone()
+            for v, s in enumerate(deltas):
+                want[:Ts] += w[:, v, None, None] * recon(s, l, kv).transpose(0, 1)
+            have = got[l, kv][rows[1][0], rows[1][1]]
+            assert (have.double() - want).abs().max() <= 1e-2 * want.abs().max()
+            assert torch.equal(have[Ts:], pool[l, kv][rows[0][0], rows[0][1]][Ts:])
+    assert (dist.cpu().double() - square.sqrt()).abs().max() <= 1e-4 * square.sqrt().max()
+
+
+@pytest.mark.parametrize("dtype,d,style", [(torch.bfloat16, 128, 0), (torch.bfloat16, 128, 1), (torch.bfloat16, 64, 2),
+                                           (torch.float32, 128, 0), (torch.float32, 64, 1)])
+def test_one_item_equals_the_same_item_in_a_batch(dtype, d, style):
+    L, H, T, r, bs = 2, 3, 333, 12, 16
+    need = -(-(T + 7) // bs)
+    pool, ids, g = _pools(L, H, d, bs, 4 * need, dtype, d + style)
+    inv = [1e4 ** (-2.0 * i / d) for i in range(d // 2)] if style else None
+    tabs = [ids[i * need:(i + 1) * need].to(torch.int32) for i in range(4)]
+    coef = [torch.randn(L, 2, H, T, r, generator=g).to(dtype) for _ in range(2)]
+    basis = [torch.randn(L, 2, H, r, d, generator=g) for _ in range(2)]
+    found = []
+    for n in (1, 2):
+        dev = pool.cuda()
+        cache = kvc.Cache([dev[l, 0] for l in range(L)], [dev[l, 1] for l in range(L)], rope_style=style,
+                          rope_inv_freq=inv)
+        st = [kvc.State(coef[i].cuda(), basis[i].cuda()) for i in range(n)]
+        out = [kvc.State.empty(L, H, d, T, r, dtype, "cuda") for _ in range(n)]
+        args = ([T] * n, [7] * n, [2] * n)
+        tables = (torch.stack(tabs[0:2][:n]).cuda(), torch.stack(tabs[2:4][:n]).cuda())
+        pos = dict(src_positions=[4] * n, dst_positions=[90] * n) if style else {}
+        kvc.kvc_fit_state(cache, kvc.Batch(*args, out, *tables, **pos))
+        kvc.kvc_apply(cache, kvc.Batch(*args, st, *tables, **pos))
+        blocks = tabs[2].long()
+        found.append((dev.cpu()[:, :, blocks], out[0].coef.cpu(), out[0].basis.cpu(), out[0].sigma.cpu()))
+    assert torch.equal(found[0][0], found[1][0])
+    # the Gram's ranges (and so its sums) may differ between the two batches: compare the products
+    a = [torch.matmul(f[1].double(), f[2].double()) for f in found]
+    assert (a[0] - a[1]).abs().max() <= 2e-2 * a[0].abs().max()
+    assert (found[0][3] - found[1][3]).abs().max() <= 1e-4 * found[0][3].max()
