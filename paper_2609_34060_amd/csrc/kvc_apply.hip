@@ -384,6 +384,32 @@ __global__ __launch_bounds__(kApplyThreads) void apply_f32_mfma(ApplyArgs a, int
     }
   };
 
+  // the source rotated by pd - ps: both features of a pair are in the lane
+  auto rotate = [&](f32x4* v) __attribute__((always_inline)) {
+    const float *c = s_rope[0], *s = s_rope[1];
+    if (style == KVC_ROPE_HALF) {
+#pragma unroll
+      for (int m = 0; m < MT / 2; ++m)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int i = 16 * m + 4 * g + e;
+          const float x = v[m][e], y = v[m + MT / 2][e];
+          v[m][e] = rope_rotated(true, x, y, c[i], s[i]);
+          v[m + MT / 2][e] = rope_rotated(false, y, x, c[i], s[i]);
+        }
+    } else {
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int e = 0; e < 4; e += 2) {
+          const int i = (16 * m + 4 * g + e) >> 1;
+          const float x = v[m][e], y = v[m][e + 1];
+          v[m][e] = rope_rotated(true, x, y, c[i], s[i]);
+          v[m][e + 1] = rope_rotated(false, y, x, c[i], s[i]);
+        }
+    }
+  };
+
   Tile cur;
   if (tile_t0(0) >= t_end) return;  // whole wave; the kernel has no barrier below
   load_tile(0, cur);
@@ -395,30 +421,7 @@ __global__ __launch_bounds__(kApplyThreads) void apply_f32_mfma(ApplyArgs a, int
     f32x4 acc[MT];
 #pragma unroll
     for (int m = 0; m < MT; ++m) acc[m] = cur.raw[m];
-    if (shift) {  // the source rotated by pd - ps: both features of a pair are in the lane
-      const float *c = s_rope[0], *s = s_rope[1];
-      if (style == KVC_ROPE_HALF) {
-#pragma unroll
-        for (int m = 0; m < MT / 2; ++m)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int i = 16 * m + 4 * g + e;
-            const float x = acc[m][e], y = acc[m + MT / 2][e];
-            acc[m][e] = rope_rotated(true, x, y, c[i], s[i]);
-            acc[m + MT / 2][e] = rope_rotated(false, y, x, c[i], s[i]);
-          }
-      } else {
-#pragma unroll
-        for (int m = 0; m < MT; ++m)
-#pragma unroll
-          for (int e = 0; e < 4; e += 2) {
-            const int i = (16 * m + 4 * g + e) >> 1;
-            const float x = acc[m][e], y = acc[m][e + 1];
-            acc[m][e] = rope_rotated(true, x, y, c[i], s[i]);
-            acc[m][e + 1] = rope_rotated(false, y, x, c[i], s[i]);
-          }
-      }
-    }
+    if (shift) rotate(acc);
     if (t0 < Ts) {  // uniform over the wave
 #pragma unroll
       for (int m = 0; m < MT; ++m)
@@ -429,6 +432,12 @@ __global__ __launch_bounds__(kApplyThreads) void apply_f32_mfma(ApplyArgs a, int
           for (int e = 0; e < 4; ++e)
             acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], cur.c[q][e], acc[m], 0, 0, 0);
         }
+      if (shift && t >= Ts) {  // in the tile where the coverage ends: rows past it take nothing of the product (zero
+                               // coefficients make a NaN of an infinite basis entry)
+#pragma unroll
+        for (int m = 0; m < MT; ++m) acc[m] = cur.raw[m];
+        rotate(acc);
+      }
     }
     if (cur.dof >= 0) {
       // rows past T_s: with a shift the rotated source, else bit copies

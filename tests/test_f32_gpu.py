@@ -91,6 +91,27 @@ def test_apply_f32_edges(d, r, T, Ts, bs, style, layerwise):
             assert torch.equal(keep, s.pool[l, kv])
 
 
+@pytest.mark.parametrize("bad", [math.inf, math.nan])
+@pytest.mark.parametrize("d,style,layerwise", [(64, 1, False), (64, 2, True), (128, 2, False), (128, 1, True)])
+def test_apply_f32_uncovered_rows_of_a_tile_ignore_the_state(d, style, layerwise, bad):
+    """Keys of a rotary cache that move, a coverage that ends inside a 16-token tile and a basis with a non-finite entry:
+    the rows past the coverage are the rotated source all the same (two fp32 products and a sum per feature: below 1e-6 of
+    the largest value), while every covered row of that unit takes the entry in."""
+    L, H, T, Ts, r, bs = 1, 2, 91, 69, 6, 16
+    s = _Setup(L, H, d, T, bs, style, 3 * d + style)
+    g = torch.Generator().manual_seed(d)
+    coef = torch.randn((L, 2, Ts, r) if layerwise else (L, 2, H, Ts, r), generator=g)
+    basis = torch.randn((L, 2, r, H, d) if layerwise else (L, 2, H, r, d), generator=g)
+    basis[..., 5] = torch.where(torch.arange(r).view((-1, 1) if layerwise else (-1,)) == 2, bad, basis[..., 5])
+    kvc.kvc_apply(s.cache, s.batch(kvc.State(coef.cuda(), basis.cuda())))
+    got = s.dev.cpu()
+    have = s.side(got, 0, 0, 1)
+    want = _rotate(s.side(s.pool, 0, 0, 0, canonical=True), style, s.pos[1])
+    assert (have[Ts:] - want[Ts:]).abs().max() <= 1e-6 * want.abs().max()
+    assert not torch.isfinite(have[:Ts]).all(dim=-1).any()
+    assert torch.equal(s.side(got, 0, 1, 1)[Ts:], s.side(s.pool, 0, 1, 0)[Ts:])
+
+
 @pytest.mark.parametrize("d,r,T,bs,style,base", [
     (64, 8, 256, 16, 0, False), (64, 3, 17, 8, 0, True), (64, 16, 65, 24, 1, False), (64, 48, 1030, 16, 2, False),
     (128, 17, 33, 16, 0, False), (128, 32, 600, 5, 1, False), (128, 64, 515, 64, 2, False),
