@@ -668,7 +668,10 @@ __device__ __forceinline__ void stage_stacked(const AnchorArgs& a, int64_t unit,
 // tile).  For that every load is unconditional (a branch around a load makes the compiler wait for more than it needs):
 // VEC (ranks multiples of 8, an anchor's coefficients of one unit within 4 GiB) reads clamped rows and ranks, whose
 // products meet zero basis rows or are masked where they would count, and chunks past the last one read it again.  Other
-// ranks take the guarded element loads.
+// ranks take guarded element loads of the chunks that there are (8 layers x 8 heads x 4096 tokens, three anchors of rank
+// 12, gate / weights / apply: 178 / 773 / 219 us with every padding chunk loaded, 97 / 369 / 118 us without).  Their
+// values are packed, and so waited for, at once: the apply loads each chunk behind its products, the distances a whole
+// tile's chunks together (ten anchors of rank 20: apply 301 us behind each chunk and 335 together, weights 1494 and 1212).
 template <bool VEC>
 __device__ __forceinline__ u32x4 load_chunk(const AnchorArgs& a, int c, int64_t unit, int t, int t_end, int g) {
   const int v = a.chunk_anchor[c], k0 = a.chunk_k0[c], r = a.rank[v];
@@ -767,7 +770,8 @@ __global__ __launch_bounds__(kResThreads) void apply_anchored_res_bf16(AnchorArg
   if (any) {
     if (nt > 0)
 #pragma unroll
-      for (int c = 0; c < NCM; ++c) load_c(0, c);
+      for (int c = 0; c < NCM; ++c)
+        if (VEC || c < NC) load_c(0, c);
     stage_stacked<D, false, ROPE>(a, unit, s_hi, s_lo, rope, (double)a.dst_position);
     __syncthreads();
   }
@@ -816,7 +820,7 @@ __global__ __launch_bounds__(kResThreads) void apply_anchored_res_bf16(AnchorArg
           for (int e = 0; e < 4; ++e) acc[mt][e] = fmaf(wc, p[e], acc[mt][e]);
         }
       }
-      load_c(jn, c);
+      if (VEC || c < NC) load_c(jn, c);
     }
     if (tile_t0(j) + 16 > Ts) {  // uniform: the tile where the coverage ends
       // rows past T_s: the rotated source with a shift, else bit copies
@@ -922,7 +926,8 @@ __global__ __launch_bounds__(kResThreads) void anchor_dist_res_bf16(AnchorArgs a
     const int64_t unit = unit_index(layer, kv, h_lo, H);
     load_row(0, h_lo);
 #pragma unroll
-    for (int c = 0; c < NCM; ++c) cw[c] = load_chunk<VEC>(a, c, unit, tile_t0(0) + n, Tl, g);
+    for (int c = 0; c < NCM; ++c)
+      if (VEC || c < NC) cw[c] = load_chunk<VEC>(a, c, unit, tile_t0(0) + n, Tl, g);
   }
   for (int h = h_lo; h < h_hi; ++h) {
     if (h > h_lo) __syncthreads();  // every wave is done with the previous head's bases
@@ -974,8 +979,12 @@ __global__ __launch_bounds__(kResThreads) void anchor_dist_res_bf16(AnchorArgs a
             for (int u = 0; u < 4; ++u) dist[0][u] += (v == 4 * u + g) ? s : 0.0f;
           }
         }
-        cw[c] = load_chunk<VEC>(a, c, unit_n, tile_t0(jn) + n, Tl, g);
+        if (VEC) cw[c] = load_chunk<VEC>(a, c, unit_n, tile_t0(jn) + n, Tl, g);
       }
+      if (!VEC)
+#pragma unroll
+        for (int c = 0; c < NCM; ++c)
+          if (c < NC) cw[c] = load_chunk<VEC>(a, c, unit_n, tile_t0(jn) + n, Tl, g);
       if constexpr (!GATE) rotate_dist();
     }
     if constexpr (!GATE)
