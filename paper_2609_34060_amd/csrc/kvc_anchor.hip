@@ -1098,7 +1098,11 @@ static bool res_vec(const AnchorArgs& a) {
   return true;
 }
 
-// Chunk counts are rounded up to the instantiated 4, 7 and 10 (a padding chunk costs its loads, which hit the cache).
+// Chunk counts are rounded up to the instantiated 4, 7 and 10: a padding chunk costs its loads, which hit the cache.
+// Rank 32, 8 layers x 8 heads x 4096 tokens, us of gate / weights / apply so and with a count's own instantiation: 3 chunks
+// 48 / 184 / 95 and 48 / 184 / 93, 5 chunks 73 / 304 / 116 and 68 / 292 / 109, 8 chunks 147 / 592 / 168 and 146 / 581 /
+// 167, 9 chunks 129 / 479 / 168 and 120 / 497 / 165.  The apply, with the fewest instructions per chunk, has one for 2 as
+// well (4 layers, one chunk 42.1 us padded to 4 and 38.7 to 2, two 49.8 and 44.4; 1000 tokens, two 27.9 and 25.6).
 template <int D, bool GATE, bool ROPE>
 static hipError_t launch_dist_res(const AnchorArgs& a, dim3 grid, size_t lds, hipStream_t stream) {
   if (!res_vec(a))
@@ -1124,6 +1128,7 @@ static hipError_t launch_anchored_res(const AnchorArgs& a, dim3 grid, size_t lds
   if (!res_vec(a))
     return launch_with_lds(apply_anchored_res_bf16<D, ROPE, kResMaxChunks, false>, grid, lds, a, stream, kResThreads);
   const int nc = a.num_chunks;
+  if (nc <= 2) return launch_with_lds(apply_anchored_res_bf16<D, ROPE, 2, true>, grid, lds, a, stream, kResThreads);
   if (nc <= 4) return launch_with_lds(apply_anchored_res_bf16<D, ROPE, 4, true>, grid, lds, a, stream, kResThreads);
   if (nc <= 7) return launch_with_lds(apply_anchored_res_bf16<D, ROPE, 7, true>, grid, lds, a, stream, kResThreads);
   return launch_with_lds(apply_anchored_res_bf16<D, ROPE, 10, true>, grid, lds, a, stream, kResThreads);

@@ -23,7 +23,7 @@ def _pools(L, H, d, bs, blocks, dtype, seed):
 @pytest.mark.parametrize("d,ranks", [
     (128, (32,)), (128, (32, 16, 8, 32)), (128, (8,) * 5), (128, (32,) * 7), (128, (24,) * 8), (64, (32,) * 10),
     (128, (64, 32)), (128, (40, 96, 8)), (128, (64,) * 5), (128, (5, 32, 17)), (64, (33, 64, 1)), (128, (12,) * 9),
-    (128, (3,)), (64, (7, 2, 20)), (128, (20,) * 10)])
+    (128, (24, 8)), (64, (64,)), (128, (3,)), (64, (7, 2, 20)), (128, (20,) * 10)])
 def test_resident_anchor_chunk_counts(d, ranks):
     L, H, T, Ts, bs = 1, 2, 1201, 1187, 16
     need = -(-(T + 5) // bs)
