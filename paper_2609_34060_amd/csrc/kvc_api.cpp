@@ -592,7 +592,11 @@ kvc_status kvc_apply(const kvc_cache* cache, const kvc_batch* batch, int32_t lay
       ai.items = device_items(batch, i0);
       ai.src_tables = batch->src_tables ? batch->src_tables + static_cast<int64_t>(i0) * batch->max_blocks : nullptr;
       ai.dst_tables = batch->dst_tables ? batch->dst_tables + static_cast<int64_t>(i0) * batch->max_blocks : nullptr;
-      s = hip_status(kvc::launch_apply(ai, cache->dtype, max_rank, max_tokens, n, stream));
+      int64_t key_chunks = 0;
+      for (int32_t i = i0; i < i0 + n; ++i)
+        key_chunks += (static_cast<int64_t>(batch->items[i].num_tokens) + kvc::kApplyRopeChunkTokens - 1) /
+                      kvc::kApplyRopeChunkTokens;
+      s = hip_status(kvc::launch_apply(ai, cache->dtype, max_rank, max_tokens, n, key_chunks, stream));
       if (s != KVC_OK) return s;
     }
   }

@@ -30,7 +30,7 @@ constexpr int kApplyWaves = 4;
 constexpr int kApplyThreads = kApplyWaves * kWave;
 constexpr int kApplyF32Tiles = 4;                                       // float32 kernel: 16-token tiles per wave
 constexpr int kApplyChunkTokens = 256;                                  // bf16 kernel: tokens per workgroup
-constexpr int kApplyRopeChunkTokens = 1024, kApplyRopeFill = 2048;      // the same with rotary keys (see the launcher)
+constexpr int kApplyRopeJointTokens = 512;                              // rotary keys and values in one launch
 
 // LDS of the bf16 kernel: basis hi/lo [D][KP] each, then the block-table slices of the workgroup's token chunk for
 // the source and the destination sequence (nblk entries each: a chunk of c tokens spans at most c / bs + 1 blocks).
@@ -463,15 +463,35 @@ static hipError_t launch_bf16_w(const ApplyArgs& a, dim3 grid, int tpw, int nblk
 // Waves per workgroup for a rank of KS 32-rank chunks.
 constexpr int apply_waves(int ks) { return ks == 1 ? 8 : 4; }
 
+// Whether keys and values of a rotary cache (head_dim 128, ranks up to 32) go in one launch of the rotary kernel, in
+// 512-token chunks of 8 waves, instead of a launch each.  The joint launch saves a launch and has short serial chains
+// (4 tiles a wave instead of 16).  The separate ones run the values at more waves per SIMD, which wins once the chip is
+// full (896 workgroups of 1024 tokens with keys), and share the angle tables and the staged basis among twice the
+// tokens, if the 1024-token chunks are filled: with two joint chunks per item, or four, and most if the last of them is
+// short or items differ in length, the line lies lower; with one chunk the values are little work for the rotary
+// kernel's setup. Time in separate launches and in one, us (8 heads; in brackets the workgroups with keys).  Up to 200
+// workgroups: 5-55 % less in one, at every size measured but 24 layers x 520 tokens, 46 and 49.  One chunk: 32 x 500
+// (256) 43 and 37, 48 items of 120 tokens (384) 33 and 35.  Two: 28 x 520 (224) 46 and 62, 32 x 700 (256) 56 and 64, 24
+// items of 700 on two layers (384) 96 and 115; the last at least 5/8 full: 32 x 1024 (256) 86 and 78, 48 x 1024 (384)
+// 124 and 128, 64 x 1024 (512) 145 and 168.  Four: 16 x 1600 (256) 68 and 60, 32 x 1540 (512) 126 and 144, 12 items of
+// up to 2048 on two layers (about 280) 88 and 94; the last at least 5/8 full: 32 x 1900 (512) 141 and 141, 40 x 2048
+// (640) 207 and 188.  Three (a 1024-token chunk half empty, so the line lies higher): 32 x 1300 (512) 117 and 103, 43
+// items of up to 1338 on three layers (1320) 301 and 256.  Others: 28 x 4 heads x 3328 (448) 125 and 106, 32 x 2500
+// (768) 195 and 179, 8 x 14656 (960) 247 and 260, 32 x 4096 (1024) 263 and 286.
+static bool rope_joint(int max_tokens, int num_items, int64_t key_groups) {
+  const int c = (max_tokens + kApplyRopeJointTokens - 1) / kApplyRopeJointTokens;
+  const bool short_last = max_tokens - (c - 1) * kApplyRopeJointTokens < kApplyRopeJointTokens * 5 / 8;
+  if ((c == 2 && short_last) || ((c == 2 || c == 4) && num_items > 1)) return key_groups < 200;
+  return key_groups < (c <= 2 || (c == 4 && short_last) ? 384 : c == 3 ? 1400 : 896);
+}
+
 // Keys of a rotary cache: every workgroup forms fp64 angle tables and stages a rotated basis, which a 1024-token chunk
 // (4 waves of 16 tiles) amortises; values (and every unit of a plain cache) take 256-token chunks in a launch of the
-// plain kernel, which runs more waves per SIMD.  While the keys alone leave the chip unfilled (below kApplyRopeFill
-// workgroups), with head_dim 128 and ranks up to 32, keys and values go in one launch of the rotary kernel in 512-token
-// chunks of 8 waves instead (two launches -> one: 28 layers x 4 heads x 3328 tokens, 448 key workgroups, 130 -> 112 us; 2
-// layers x 4 heads x 600 tokens 35 -> 20 us; 32 x 8 x 16384, 4096 of them, 992 -> 1093 us; rank 64 158 -> 160 us; head_dim
-// 64 63 -> 72 us).
+// plain kernel, which runs more waves per SIMD.  Small launches take both sides at once (rope_joint; not at rank 64,
+// 158 -> 160 us, or head_dim 64, 63 -> 72 us, on 28 layers x 4 heads x 3328 tokens).
 template <int D, int KS>
-static hipError_t launch_bf16(const ApplyArgs& a0, int max_tokens, int num_items, hipStream_t stream) {
+static hipError_t launch_bf16(const ApplyArgs& a0, int max_tokens, int num_items, int64_t key_chunks,
+                              hipStream_t stream) {
   ApplyArgs a = a0;
   const int H = a.pv.num_kv_heads, il = num_items * a.num_layers;
   auto launch = [&](auto rope, auto waves, int chunk, int kv_begin, int nkv) {
@@ -484,22 +504,22 @@ static hipError_t launch_bf16(const ApplyArgs& a0, int max_tokens, int num_items
   };
   using Plain = std::integral_constant<int, apply_waves(KS)>;
   if (a.pv.rope.style == KVC_ROPE_NONE) return launch(std::false_type{}, Plain{}, kApplyChunkTokens, 0, 2);
-  const int64_t key_groups = (int64_t)((max_tokens + kApplyRopeChunkTokens - 1) / kApplyRopeChunkTokens) * H * il;
   if constexpr (KS == 1 && D == 128)
-    if (key_groups < kApplyRopeFill)
-      return launch(std::true_type{}, std::integral_constant<int, 8>{}, kApplyRopeChunkTokens / 2, 0, 2);
+    if (rope_joint(max_tokens, num_items, key_chunks * H * a.num_layers))
+      return launch(std::true_type{}, std::integral_constant<int, 8>{}, kApplyRopeJointTokens, 0, 2);
   const hipError_t e = launch(std::true_type{}, std::integral_constant<int, 4>{}, kApplyRopeChunkTokens, 0, 1);
   return e != hipSuccess ? e : launch(std::false_type{}, Plain{}, kApplyChunkTokens, 1, 1);
 }
 
 template <int D>
-static hipError_t launch_bf16_ks(const ApplyArgs& a, int ks, int max_tokens, int num_items, hipStream_t stream) {
+static hipError_t launch_bf16_ks(const ApplyArgs& a, int ks, int max_tokens, int num_items, int64_t key_chunks,
+                                 hipStream_t stream) {
   switch (ks) {
     case 0:
-    case 1: return launch_bf16<D, 1>(a, max_tokens, num_items, stream);
-    case 2: return launch_bf16<D, 2>(a, max_tokens, num_items, stream);
-    case 3: return launch_bf16<D, 3>(a, max_tokens, num_items, stream);
-    default: return launch_bf16<D, 4>(a, max_tokens, num_items, stream);
+    case 1: return launch_bf16<D, 1>(a, max_tokens, num_items, key_chunks, stream);
+    case 2: return launch_bf16<D, 2>(a, max_tokens, num_items, key_chunks, stream);
+    case 3: return launch_bf16<D, 3>(a, max_tokens, num_items, key_chunks, stream);
+    default: return launch_bf16<D, 4>(a, max_tokens, num_items, key_chunks, stream);
   }
 }
 
@@ -531,13 +551,13 @@ static hipError_t launch_f32_kq(const ApplyArgs& a, int kq, int max_tokens, int 
 }
 
 hipError_t launch_apply(const ApplyArgs& a, kvc_dtype dtype, int max_rank, int max_tokens, int num_items,
-                        hipStream_t stream) {
+                        int64_t key_chunks, hipStream_t stream) {
   if (max_tokens == 0 || num_items == 0 || a.num_layers == 0) return hipSuccess;
   const int D = a.pv.head_dim;
   if (dtype == KVC_BF16) {
     const int ks = (max_rank + 31) / 32;
-    return D == 64 ? launch_bf16_ks<64>(a, ks, max_tokens, num_items, stream)
-                   : launch_bf16_ks<128>(a, ks, max_tokens, num_items, stream);
+    return D == 64 ? launch_bf16_ks<64>(a, ks, max_tokens, num_items, key_chunks, stream)
+                   : launch_bf16_ks<128>(a, ks, max_tokens, num_items, key_chunks, stream);
   }
   return D == 64 ? launch_f32_kq<64>(a, (max_rank + 15) / 16, max_tokens, num_items, stream)
                  : launch_f32_kq<128>(a, (max_rank + 15) / 16, max_tokens, num_items, stream);

@@ -63,8 +63,11 @@ __device__ __forceinline__ kvc_item item_of(const Args& a, int i) {
   return a.items ? a.items[i] : a.one;
 }
 
+// key_chunks: kApplyRopeChunkTokens-token chunks of the launch's items (workgroups per head and layer of a launch over
+// rotary keys alone).
+constexpr int kApplyRopeChunkTokens = 1024;
 hipError_t launch_apply(const ApplyArgs& a, kvc_dtype dtype, int max_rank, int max_tokens, int num_items,
-                        hipStream_t stream);
+                        int64_t key_chunks, hipStream_t stream);
 
 // Fit (kvc_fit.hip): Gram partials, then projection after the eigensolver.
 // A partial Gram is stored as the accumulator fragments of its upper tiles, [tile][lane] of four floats in the order of

@@ -99,3 +99,35 @@ def test_one_item_equals_the_same_item_in_a_batch(dtype, d, style):
     a = [torch.matmul(f[1].double(), f[2].double()) for f in found]
     assert (a[0] - a[1]).abs().max() <= 2e-2 * a[0].abs().max()
     assert (found[0][3] - found[1][3]).abs().max() <= 1e-4 * found[0][3].max()
+
+
+@pytest.mark.parametrize("lengths,L", [
+    ((100,), 47), ((100,), 48), ((520,), 24), ((520,), 25), ((900,), 47), ((900,), 48), ((1030,), 87), ((1030,), 88),
+    ((1540,), 23), ((1540,), 24), ((2048,), 25), ((2300,), 37), ((2300,), 38), ((700, 130, 512) * 4, 2),
+    ((700, 130, 512) * 4 + (1,), 2), ((1700, 400) * 4, 2), ((1700, 400) * 5, 2), ((1300, 1025, 3) * 5, 1)])
+def test_rotary_apply_in_one_launch_or_two(lengths, L):
+    """Sizes on both sides of the lines between a joint launch of keys and values and separate ones: a call over all
+    layers equals calls of one layer each (whose few workgroups take the joint launch), bit for bit."""
+    H, d, r, bs, n = 8, 128, 20, 16, len(lengths)
+    need = -(-(max(lengths) + 7) // bs)
+    g = torch.Generator(device="cuda").manual_seed(L + n)
+    pool = torch.randn(L, 2, 2 * n * need, bs, H, d, generator=g, device="cuda").to(torch.bfloat16)
+    ids = torch.randperm(2 * n * need, generator=g, device="cuda").to(torch.int32).view(2, n, need)
+    st = []
+    for t in lengths:
+        ts = max(1, t - 5)
+        st.append(kvc.State(torch.randn(L, 2, H, ts, r, generator=g, device="cuda").to(torch.bfloat16),
+                            torch.randn(L, 2, H, r, d, generator=g, device="cuda")))
+    batch = kvc.Batch(lengths, [7] * n, [3] * n, st, ids[0], ids[1], src_positions=[4 + i for i in range(n)],
+                      dst_positions=[90] * n)
+    inv = [1e4 ** (-2.0 * i / d) for i in range(d // 2)]
+    got = []
+    for step in (L, 1):
+        dev = pool.clone()
+        cache = kvc.Cache([dev[l, 0] for l in range(L)], [dev[l, 1] for l in range(L)], rope_style=kvc.KVC_ROPE_HALF,
+                          rope_inv_freq=inv)
+        for l in range(0, L, step):
+            kvc.kvc_apply(cache, batch, l, l + step)
+        got.append(dev)
+    assert torch.equal(got[0], got[1])
+    assert not torch.equal(got[0], pool)
