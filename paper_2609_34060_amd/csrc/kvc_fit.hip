@@ -653,9 +653,8 @@ __host__ __device__ constexpr size_t proj_lds_bytes(int D, int RP, int nblk) {
   return (size_t)2 * RP * D * 2 + (size_t)2 * nblk * 4;
 }
 
-// (head_dim 64: six waves per SIMD, three workgroups of eight a CU)
 template <int D, int MTR, int W, bool ROPE>
-__global__ __launch_bounds__(W * kWave, D == 64 && !ROPE && MTR <= 4 ? 6 : 1) void proj_bf16_mfma(FitArgs a, int tpw, int nblk) {
+__global__ __launch_bounds__(W * kWave) void proj_bf16_mfma(FitArgs a, int tpw, int nblk) {
   constexpr int KS = D / 32;          // K-steps over features
   constexpr int RP = MTR * 16;        // padded rank
   extern __shared__ __attribute__((aligned(16))) uint16_t s_dyn[];
