@@ -563,6 +563,14 @@ constexpr int kResThreads = kResWaves * kWave;
 constexpr int kResTiles = 16, kResDistTiles = 8;
 constexpr int kResChunk = kResWaves * kResTiles * 16;
 constexpr int kResDistChunk = kResWaves * kResDistTiles * 16;
+// The apply of a single chunk stages little per workgroup (16 KB of basis at head_dim 128) and is bound by memory, so
+// shorter workgroups, which balance better, cost it nothing: 2 tiles (256 tokens), and 8 with rotary keys, whose
+// workgroups form fp64 angles first.  One anchor of rank 32, 8 heads, us with 16 / 8 / 4 / 2 tiles: 4 layers x 1000 tokens
+// 20 / 20 / 13 / 10, 8 x 2048 36 / 28 / 28 / 31, 8 x 4096 70 / 72 / 72 / 71, 8 x 8192 145 / 144 / 135 / 132, 28 x 3328
+// 245 / 222 / 183 / 186, 32 x 4096 282 / 279 / 273 / 265; rotary 25 / 25 / 17 / 13, 44 / 32 / 33 / 40, 72 / 73 / 75 / 83,
+// 143 / 143 / 140 / 162, 246 / 228 / 191 / 222, 278 / 282 / 285 / 321.  (Ten chunks in registers at two waves per SIMD
+// took 69, 140, 234 and 272 us at the last four plain sizes.)
+constexpr int res_apply_tiles(bool rope, int ncm) { return ncm > 1 ? kResTiles : rope ? 8 : 2; }
 int anchor_resident_chunk_tokens() { return kResDistChunk; }  // the shorter chunk (more partials)
 constexpr size_t kResMaxLds = 160 * 1024;
 
@@ -718,7 +726,8 @@ __device__ __forceinline__ void row_f32(const u32x4* raw, f32x4* x) {
 // 32 layers x 8 heads x 4096 tokens, ten anchors of rank 32: 680 us before the rolling loads, 649 us with them.
 template <int D, bool ROPE, int NCM, bool VEC>
 __global__ __launch_bounds__(kResThreads) void apply_anchored_res_bf16(AnchorArgs a) {
-  constexpr int MT = D / 16, NQ = D / 32;
+  constexpr int MT = D / 16, NQ = D / 32, TPW = res_apply_tiles(ROPE, NCM);
+  constexpr int CH = kResWaves * TPW * 16;  // tokens per workgroup
   extern __shared__ __attribute__((aligned(16))) unsigned char anchor_lds[];
   const int NC = a.num_chunks, kpt = 32 * NC;
   uint16_t* s_hi = reinterpret_cast<uint16_t*>(anchor_lds);
@@ -728,7 +737,7 @@ __global__ __launch_bounds__(kResThreads) void apply_anchored_res_bf16(AnchorArg
   const int H = a.pv.num_kv_heads;
   const int kv = blockIdx.y / H, head = blockIdx.y - kv * H;
   const int T = a.num_tokens, Ts = a.num_weighted, V = a.num_anchors;
-  const int t_begin = blockIdx.x * kResChunk;
+  const int t_begin = blockIdx.x * CH;
   if (t_begin >= T) return;  // whole workgroup
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = threadIdx.x % kWave, g = lane >> 4, n = lane & 15;
@@ -741,12 +750,12 @@ __global__ __launch_bounds__(kResThreads) void apply_anchored_res_bf16(AnchorArg
   const bool shift = rope && a.dst_position != a.src_position;
   float tc = 1.0f, ts = 0.0f;  // this lane's entry of the wave's angle table for pd - ps
   if (shift) rope_wave_table<D>(a.pv.rope, (double)a.dst_position - (double)a.src_position, lane, tc, ts);
-  const int t_end = min(T, t_begin + kResChunk);
+  const int t_end = min(T, t_begin + CH);
   const LaneTable lts = lane_table(a.pv, a.src_table, a.src_offset, t_begin, t_end, lane);
   const LaneTable ltd = lane_table(a.pv, a.dst_table, a.dst_offset, t_begin, t_end, lane);
   const bool any = t_begin < Ts;  // uniform over the workgroup
   // tiles of this wave: rows t0 + n, t0 = t_begin + (j kResWaves + wave) 16
-  const int nt = max(0, min(kResTiles, (t_end - t_begin - wave * 16 + kResWaves * 16 - 1) / (kResWaves * 16)));
+  const int nt = max(0, min(TPW, (t_end - t_begin - wave * 16 + kResWaves * 16 - 1) / (kResWaves * 16)));
   auto tile_t0 = [&](int j) { return t_begin + (j * kResWaves + wave) * 16; };
 
   u32x4 raw[NQ], cw[NCM];
@@ -1102,7 +1111,8 @@ static bool res_vec(const AnchorArgs& a) {
 // Rank 32, 8 layers x 8 heads x 4096 tokens, us of gate / weights / apply so and with a count's own instantiation: 3 chunks
 // 48 / 184 / 95 and 48 / 184 / 93, 5 chunks 73 / 304 / 116 and 68 / 292 / 109, 8 chunks 147 / 592 / 168 and 146 / 581 /
 // 167, 9 chunks 129 / 479 / 168 and 120 / 497 / 165.  The apply, with the fewest instructions per chunk, has one for 2 as
-// well (4 layers, one chunk 42.1 us padded to 4 and 38.7 to 2, two 49.8 and 44.4; 1000 tokens, two 27.9 and 25.6).
+// well (4 layers, two chunks 49.8 us padded to 4 and 44.4; 1000 tokens 27.9 and 25.6), and one for a single chunk
+// (res_apply_tiles).
 template <int D, bool GATE, bool ROPE>
 static hipError_t launch_dist_res(const AnchorArgs& a, dim3 grid, size_t lds, hipStream_t stream) {
   if (!res_vec(a))
@@ -1123,15 +1133,22 @@ static hipError_t launch_dist_res(const AnchorArgs& a, dim3 grid, size_t lds, hi
   return launch_with_lds(anchor_dist_res_bf16<D, GATE, ROPE, 10, true, false>, grid, lds, a, stream, kResThreads);
 }
 
+template <int D, bool ROPE, int NCM, bool VEC>
+static hipError_t launch_anchored_chunks(const AnchorArgs& a, size_t lds, hipStream_t stream) {
+  constexpr int kTokens = kResWaves * res_apply_tiles(ROPE, NCM) * 16;
+  const dim3 grid((a.num_tokens + kTokens - 1) / kTokens, 2 * a.pv.num_kv_heads, a.num_layers);
+  return launch_with_lds(apply_anchored_res_bf16<D, ROPE, NCM, VEC>, grid, lds, a, stream, kResThreads);
+}
+
 template <int D, bool ROPE>
-static hipError_t launch_anchored_res(const AnchorArgs& a, dim3 grid, size_t lds, hipStream_t stream) {
-  if (!res_vec(a))
-    return launch_with_lds(apply_anchored_res_bf16<D, ROPE, kResMaxChunks, false>, grid, lds, a, stream, kResThreads);
+static hipError_t launch_anchored_res(const AnchorArgs& a, size_t lds, hipStream_t stream) {
+  if (!res_vec(a)) return launch_anchored_chunks<D, ROPE, kResMaxChunks, false>(a, lds, stream);
   const int nc = a.num_chunks;
-  if (nc <= 2) return launch_with_lds(apply_anchored_res_bf16<D, ROPE, 2, true>, grid, lds, a, stream, kResThreads);
-  if (nc <= 4) return launch_with_lds(apply_anchored_res_bf16<D, ROPE, 4, true>, grid, lds, a, stream, kResThreads);
-  if (nc <= 7) return launch_with_lds(apply_anchored_res_bf16<D, ROPE, 7, true>, grid, lds, a, stream, kResThreads);
-  return launch_with_lds(apply_anchored_res_bf16<D, ROPE, 10, true>, grid, lds, a, stream, kResThreads);
+  if (nc == 1) return launch_anchored_chunks<D, ROPE, 1, true>(a, lds, stream);
+  if (nc == 2) return launch_anchored_chunks<D, ROPE, 2, true>(a, lds, stream);
+  if (nc <= 4) return launch_anchored_chunks<D, ROPE, 4, true>(a, lds, stream);
+  if (nc <= 7) return launch_anchored_chunks<D, ROPE, 7, true>(a, lds, stream);
+  return launch_anchored_chunks<D, ROPE, 10, true>(a, lds, stream);
 }
 
 template <int D, bool GATE, bool ROPE>
@@ -1219,10 +1236,8 @@ static hipError_t launch_anchored_variant(const AnchorArgs& a, kvc_dtype dtype, 
   if (dtype == KVC_BF16) {
     AnchorArgs r = a;
     if (plan_resident(r)) {
-      dim3 grid((a.num_tokens + kResChunk - 1) / kResChunk, 2 * a.pv.num_kv_heads, a.num_layers);
       const size_t rl = res_lds_bytes(r, 1);
-      return D == 64 ? launch_anchored_res<64, ROPE>(r, grid, rl, stream)
-                     : launch_anchored_res<128, ROPE>(r, grid, rl, stream);
+      return D == 64 ? launch_anchored_res<64, ROPE>(r, rl, stream) : launch_anchored_res<128, ROPE>(r, rl, stream);
     }
     dim3 grid((a.num_tokens + kAnchoredChunk - 1) / kAnchoredChunk, 2 * a.pv.num_kv_heads, a.num_layers);
     return D == 64 ? launch_anchored_bf16<64, ROPE>(a, grid, lds, stream)

@@ -70,6 +70,40 @@ def test_resident_anchor_chunk_counts(d, ranks):
     assert (dist.cpu().double() - square.sqrt()).abs().max() <= 1e-4 * square.sqrt().max()
 
 
+@pytest.mark.parametrize("style,bs,d,T,Ts", [
+    (0, 16, 128, 1100, 1000), (0, 1, 64, 600, 590), (1, 16, 128, 2101, 1030), (2, 4, 64, 1500, 1490), (2, 16, 128, 9, 9)])
+def test_one_anchor_equals_the_state_applied(style, bs, d, T, Ts):
+    """A single anchor has weight 1, so its apply (workgroups of their own lengths, with and without rotary keys; block
+    tables in registers and, for blocks of 1 and 4 tokens, in memory) is the state's: one bf16 rounding of the value, and
+    fp32 sums in another order near zero."""
+    L, H, r = 2, 2, 24
+    need = -(-(T + 5) // bs)
+    pool, ids, g = _pools(L, H, d, bs, 2 * need, torch.bfloat16, T)
+    inv = [1e4 ** (-2.0 * i / d) for i in range(d // 2)] if style else None
+    st = kvc.State(torch.randn(L, 2, H, Ts, r, generator=g).to(torch.bfloat16).cuda(),
+                   (torch.randn(L, 2, H, r, d, generator=g) / math.sqrt(r)).cuda())
+    empty = kvc.State(torch.zeros(L, 2, H, 0, 0, dtype=torch.bfloat16).cuda(), torch.zeros(L, 2, H, 0, d).cuda())
+    tabs = [ids[i * need:(i + 1) * need].to(torch.int32).view(1, -1).cuda() for i in range(2)]
+    pos = dict(src_positions=[7], dst_positions=[300]) if style else {}
+    found = []
+    for item in (empty, st):
+        dev = pool.cuda()
+        cache = kvc.Cache([dev[l, 0] for l in range(L)], [dev[l, 1] for l in range(L)], rope_style=style,
+                          rope_inv_freq=inv)
+        batch = kvc.Batch([T], [5], [2], [item], *tabs, **pos)
+        if item is empty:
+            an = kvc.Anchors([st], Ts, L)
+            kvc.kvc_anchor_weights(cache, batch, an)
+            assert bool((an.weights == 1.0).all())
+            kvc.kvc_apply_anchored(cache, batch, an)
+        else:
+            kvc.kvc_apply(cache, batch)
+        found.append(dev.cpu().float())
+    a, b = found
+    assert ((a - b).abs() <= b.abs() * 2.0 ** -7 + 2.0 ** -14).all()
+    assert not torch.equal(b, pool.float())
+
+
 @pytest.mark.parametrize("dtype,d,style", [(torch.bfloat16, 128, 0), (torch.bfloat16, 128, 1), (torch.bfloat16, 64, 2),
                                            (torch.float32, 128, 0), (torch.float32, 64, 1)])
 def test_one_item_equals_the_same_item_in_a_batch(dtype, d, style):
