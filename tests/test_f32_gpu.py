@@ -60,7 +60,20 @@ class _Setup:
     (64, 63, 129, 129, 24, 2, False), (128, 16, 63, 63, 16, 0, True), (128, 33, 300, 299, 64, 1, False),
     (128, 64, 257, 0, 5, 2, False), (128, 128, 140, 140, 32, 1, False), (128, 20, 5000, 4997, 16, 0, False)])
 def test_apply_f32_edges(d, r, T, Ts, bs, style, layerwise):
-    L, H = 2, 3
+    _check_apply(2, 3, d, r, T, Ts, bs, style, layerwise)
+
+
+# Launches of at least 1024 workgroups of 256 tokens give each wave four tiles in turn (smaller ones: a single tile, as
+# in every case above); coverages end inside the second, third and fourth tile of a wave.
+@pytest.mark.parametrize("L,H,d,r,T,Ts,bs,style,layerwise", [
+    (8, 8, 128, 20, 2101, 1999, 16, 0, False), (8, 8, 64, 7, 2099, 2061, 24, 1, False),
+    (13, 5, 128, 33, 2053, 1900, 5, 2, True)])
+def test_apply_f32_four_tiles_a_wave(L, H, d, r, T, Ts, bs, style, layerwise):
+    assert -(-T // 256) * 2 * H * L >= 1024 and T % 16 and Ts % 16
+    _check_apply(L, H, d, r, T, Ts, bs, style, layerwise)
+
+
+def _check_apply(L, H, d, r, T, Ts, bs, style, layerwise):
     s = _Setup(L, H, d, T, bs, style, 7 * T + r)
     g = torch.Generator().manual_seed(r)
     if layerwise:
@@ -117,7 +130,19 @@ def test_apply_f32_uncovered_rows_of_a_tile_ignore_the_state(d, style, layerwise
     (128, 17, 33, 16, 0, False), (128, 32, 600, 5, 1, False), (128, 64, 515, 64, 2, False),
     (128, 100, 2049, 16, 0, True)])
 def test_fit_f32_edges(d, r, T, bs, style, base):
-    L, H = 2, 3
+    _check_fit(2, 3, d, r, T, bs, style, base)
+
+
+# The projection's four tiles a wave, from 1024 workgroups of 256 tokens; the keys of a rotary cache and its values are a
+# launch each.
+@pytest.mark.parametrize("L,H,d,r,T,bs,style,base", [
+    (8, 8, 128, 18, 2099, 16, 0, False), (16, 8, 64, 7, 2085, 24, 1, False), (16, 8, 128, 33, 2053, 16, 2, True)])
+def test_fit_f32_four_tiles_a_wave(L, H, d, r, T, bs, style, base):
+    assert -(-T // 256) * (1 if style else 2) * H * L >= 1024 and T % 16
+    _check_fit(L, H, d, r, T, bs, style, base)
+
+
+def _check_fit(L, H, d, r, T, bs, style, base):
     s = _Setup(L, H, d, T, bs, style, 11 * T + r)
     st = kvc.State.empty(L, H, d, T, r, torch.float32, "cuda")
     kvc.kvc_fit_state(s.cache, s.batch(st), mode=kvc.KVC_FIT_BASE if base else kvc.KVC_FIT_DELTA)
