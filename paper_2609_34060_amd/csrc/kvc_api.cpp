@@ -190,11 +190,11 @@ FitPlan plan_fit(const kvc_cache* c, const kvc_batch* b, int32_t lb, int32_t le)
   p.off_partials = off;
   off = align256(off + p.units * p.max_parts * kvc::gram_partial_floats(c->head_dim) * sizeof(float));
   p.off_reflect = off;
-  off = align256(off + p.units * d * d * sizeof(double));
+  off = align256(off + p.units * d * d * sizeof(float));
   p.off_beta = off;
-  off = align256(off + p.units * d * sizeof(double));
+  off = align256(off + p.units * d * sizeof(float));
   p.off_vecs = off;
-  off = align256(off + p.units * KVC_MAX_RANK * d * sizeof(double));
+  off = align256(off + p.units * KVC_MAX_RANK * d * sizeof(float));
   p.total = off;
   return p;
 }
@@ -276,11 +276,11 @@ LayerPlan plan_layer_fit(const kvc_cache* c, const kvc_batch* b, int32_t lb, int
   p.off_vsigma = off;
   off = align256(off + U * KVC_MAX_RANK * sizeof(float));
   p.off_reflect = off;
-  off = align256(off + U * k * k * sizeof(double));
+  off = align256(off + U * k * k * sizeof(float));
   p.off_beta = off;
-  off = align256(off + U * k * sizeof(double));
+  off = align256(off + U * k * sizeof(float));
   p.off_vecs = off;
-  off = align256(off + U * KVC_MAX_RANK * k * sizeof(double));
+  off = align256(off + U * KVC_MAX_RANK * k * sizeof(float));
   p.off_resid = off;
   off = align256(off + U * KVC_MAX_RANK * sizeof(double));
   p.off_conv = off;
@@ -366,11 +366,11 @@ ChainPlan plan_chain(const kvc_state* a, const kvc_state* b, const kvc_state* o,
   p.off_gram = off;
   off = align256(off + U * d * d * sizeof(double));
   p.off_reflect = off;
-  off = align256(off + U * d * d * sizeof(double));
+  off = align256(off + U * d * d * sizeof(float));
   p.off_beta = off;
-  off = align256(off + U * d * sizeof(double));
+  off = align256(off + U * d * sizeof(float));
   p.off_vecs = off;
-  off = align256(off + U * KVC_MAX_RANK * d * sizeof(double));
+  off = align256(off + U * KVC_MAX_RANK * d * sizeof(float));
   p.off_ymat = off;
   off = align256(off + U * m * static_cast<size_t>(o->rank) * sizeof(float));
   p.total = off;
@@ -678,9 +678,9 @@ kvc_status fit_per_layer(const kvc_cache* cache, const kvc_batch* batch, int32_t
       ea.layer_begin = 0;
       ea.num_layers = la.num_layers;
       ea.num_kv_heads = 1;
-      ea.reflect = reinterpret_cast<double*>(ws + p.off_reflect);
-      ea.reflect_beta = reinterpret_cast<double*>(ws + p.off_beta);
-      ea.vecs = reinterpret_cast<double*>(ws + p.off_vecs);
+      ea.reflect = reinterpret_cast<float*>(ws + p.off_reflect);
+      ea.reflect_beta = reinterpret_cast<float*>(ws + p.off_beta);
+      ea.vecs = reinterpret_cast<float*>(ws + p.off_vecs);
       ea.seed = 0x1A7Eu;
       s = hip_status(kvc::launch_layer_gram(la, cache->dtype, stream));
       if (s != KVC_OK) return s;
@@ -738,9 +738,9 @@ kvc_status kvc_fit_state(const kvc_cache* cache, const kvc_batch* batch, int32_t
   ea.max_parts = p.max_parts;
   ea.part_tokens = p.part_tokens;
   ea.num_kv_heads = cache->num_kv_heads;
-  ea.reflect = reinterpret_cast<double*>(ws + p.off_reflect);
-  ea.reflect_beta = reinterpret_cast<double*>(ws + p.off_beta);
-  ea.vecs = reinterpret_cast<double*>(ws + p.off_vecs);
+  ea.reflect = reinterpret_cast<float*>(ws + p.off_reflect);
+  ea.reflect_beta = reinterpret_cast<float*>(ws + p.off_beta);
+  ea.vecs = reinterpret_cast<float*>(ws + p.off_vecs);
   ea.seed = 0x5EEDu;
   for (int32_t l0 = layer_begin; l0 < layer_end; l0 += p.layers_per_group) {
     const int32_t l1 = std::min(layer_end, l0 + p.layers_per_group);
@@ -807,9 +807,9 @@ kvc_status kvc_chain(const kvc_state* first, const kvc_state* second, kvc_state*
   ea.layer_begin = layer_begin;
   ea.num_layers = ca.num_layers;
   ea.num_kv_heads = first->num_kv_heads;
-  ea.reflect = reinterpret_cast<double*>(ws + p.off_reflect);
-  ea.reflect_beta = reinterpret_cast<double*>(ws + p.off_beta);
-  ea.vecs = reinterpret_cast<double*>(ws + p.off_vecs);
+  ea.reflect = reinterpret_cast<float*>(ws + p.off_reflect);
+  ea.reflect_beta = reinterpret_cast<float*>(ws + p.off_beta);
+  ea.vecs = reinterpret_cast<float*>(ws + p.off_vecs);
   ea.seed = 0xC4A1u;
   return hip_status(kvc::launch_chain(ca, ea, stream));
 }

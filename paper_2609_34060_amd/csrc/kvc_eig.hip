@@ -86,11 +86,6 @@ __device__ __forceinline__ float max8(float x) {
   x = fmaxf(x, dpp32<kDppXor2>(x));
   return fmaxf(x, dpp32<kDppHalfMirror>(x));
 }
-__device__ __forceinline__ int sum8i(int x) {
-  x += dpp32i<kDppXor1>(x);
-  x += dpp32i<kDppXor2>(x);
-  return x + dpp32i<kDppHalfMirror>(x);
-}
 __device__ __forceinline__ int min8(int x) {
   x = min(x, dpp32i<kDppXor1>(x));
   x = min(x, dpp32i<kDppXor2>(x));
@@ -220,8 +215,9 @@ __device__ __forceinline__ int sturm_count(const double* sa, const double* sb2, 
 // of the kTriWaves (one per SIMD) holds the tile columns W, W + kTriWaves, ..  The rank-2 update of a tile is one such
 // MFMA (K slots 0 and 1 carry {v, w} against {-w, -v}, the other two zeros), and a wave's columns of A22 v are four FMAs
 // per tile, so nothing of the matrix goes through LDS and no row scalar is broadcast to a wave.  Tiles whose rows or
-// columns have all been reduced drop out (the loop over 16-row blocks is unrolled, the inner one is not).  p, K, w, the
-// scalars and the reflectors are fp64, in one further wave, the chain wave, whose lanes own N / 64 columns each.
+// columns have all been reduced drop out (the loop over 16-row blocks is unrolled, the inner one is not).  p, K, w and
+// the scalars are computed in fp64, in one further wave, the chain wave, whose lanes own N / 64 columns each; v and w are
+// rounded to fp32 for the update, and the back-transformation uses the same fp32 v.
 //
 // Step k, with three workgroup barriers (the other waves of the workgroup only meet them):
 //   chain   brings row k up to date with the pending update of step k - 1, forms the reflector and writes v;      [1]
@@ -235,12 +231,6 @@ __device__ __forceinline__ int sturm_count(const double* sa, const double* sb2, 
 // matrix in LDS (four waves sweeping its rows, the scalars broadcast from LDS), 152 us with register tiles and every
 // wave computing the chain, 122 us so; one unit of N = 64: 52, 39 and 35 us.
 constexpr int kTriWaves = 4;
-
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // LDS of the reduction: s_op [4][N] (v, w, 0, 0 of the pending update), s_vn [N] (v of the current step), share [4][N],
 // s_row [N], the last diagonal entry.
@@ -474,9 +464,9 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(4))
   const int r = tg.rank;
   if (r <= 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  float* refl = reinterpret_cast<float*>(a.reflect + (size_t)u * N * N);  // v_k in row k, fp32
-  float* refl_beta = reinterpret_cast<float*>(a.reflect_beta + (size_t)u * N);
-  float* gvec = reinterpret_cast<float*>(a.vecs + (size_t)u * N * KVC_MAX_RANK);  // eigenvectors of T in rows, fp32
+  float* refl = a.reflect + (size_t)u * N * N;  // v_k in row k
+  float* refl_beta = a.reflect_beta + (size_t)u * N;
+  float* gvec = a.vecs + (size_t)u * N * KVC_MAX_RANK;  // eigenvectors of T in rows
 
   // ---- 1. load G ------------------------------------------------------------------------------------------
   // Every load of a partial (or of the dense matrix) is issued before its values are added, and the partials are added

@@ -147,9 +147,9 @@ struct EigArgs {
   int32_t layer_begin;
   int32_t num_layers;
   int32_t num_kv_heads;
-  double* reflect;            // workspace [unit][n][n]
-  double* reflect_beta;       // workspace [unit][n]
-  double* vecs;               // workspace [unit][KVC_MAX_RANK][n]
+  float* reflect;             // workspace [unit][n][n]
+  float* reflect_beta;        // workspace [unit][n]
+  float* vecs;                // workspace [unit][KVC_MAX_RANK][n]
   uint32_t seed;
   const int32_t* skip;        // [unit] nonzero: leave the unit's outputs as they are (null: every unit)
 };

@@ -385,6 +385,20 @@ def test_per_layer_states_are_refused_where_unsupported():
     assert ws() == 0 and fit() == kvc.KVC_ERR_UNSUPPORTED
 
 
+def test_fit_workspace_is_the_sum_of_its_fp32_arrays():
+    """Per unit: the Gram's partials (the upper 16 x 16 tiles; a multiple of four of at least 256 tokens each), the
+    eigensolver's reflectors [d][d], their scalars [d] and its eigenvectors [KVC_MAX_RANK][d], all fp32 and each array
+    rounded up to 256 bytes."""
+    f = Fixture(T=300)
+    L, H, d = f.cache.num_layers, f.cache.num_kv_heads, f.cache.head_dim
+    f.items[0].state = kvc.kvc_state(L, H, d, 300, 8, kvc.KVC_BF16, kvc.KVC_GROUP_HEAD, 0, FAKE + 0x4000000,
+                                     FAKE + 0x8000000, None)
+    units, tiles = L * 2 * H, (d // 16) * (d // 16 + 1) // 2
+    floats = [4 * tiles * 256, d * d, d, kvc.KVC_MAX_RANK * d]
+    need = kvc.load().kvc_fit_workspace_bytes(ctypes.byref(f.cache), ctypes.byref(f.batch), 0, L)
+    assert need == sum(-(-units * n * 4 // 256) * 256 for n in floats)
+
+
 def test_gate_noalloc_rejects_before_launch():
     """The allocation-free gate takes the same checks as kvc_gate_distances, and a call whose partial sums would not
     fit the static scratch is refused with KVC_ERR_TOO_LARGE before anything is enqueued."""
