@@ -152,10 +152,12 @@ struct FitPlan {
 };
 
 // Gram waves per fit launch: two rounds of a workgroup per CU for one item, whose ranges are equal; twice that for items
-// of different lengths, whose short last ranges leave CUs idle, as long as the ranges keep kGramLongRange tokens (64
-// requests of 1K-16K tokens, ranges of 2240 for 4448 tokens: Gram 1.61 -> 1.31 ms together with the shifted items of
-// chunk_grid; 24 requests of up to 6000 tokens, 320 for 608: the whole fit 0.60 -> 0.62 ms, the partials outweigh it).
-constexpr int64_t kGramWaveTarget = 2048, kGramWaveTargetItems = 4096, kGramLongRange = 1024;
+// of different lengths, whose short last ranges leave CUs idle, as long as the ranges keep kGramLongRange tokens (below,
+// the partials outweigh it).  Whole fits of one layer x 8 heads at rank 32, us with half as many ranges and so (tokens in
+// a range): 64 requests 2570 and 2446 (1952), 1655 and 1610 (1056), 1377 and 1339 (832), 1106 and 1117 (512), 808 and 830
+// (288); 16 requests 1443 and 1380 (1120), 939 and 963 (640), 675 and 729 (416); 8 requests of two layers 1111 and 1081
+// (832), 988 and 976 (704), 910 and 904 (608); 64 requests with rotary keys 1890 and 1818 (832).
+constexpr int64_t kGramWaveTarget = 2048, kGramWaveTargetItems = 4096, kGramLongRange = 704;
 
 FitPlan plan_fit(const kvc_cache* c, const kvc_batch* b, int32_t lb, int32_t le) {
   FitPlan p;
