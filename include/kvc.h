@@ -161,9 +161,10 @@ typedef struct kvc_item {
  * then copies it (hipMemcpyAsync on the call's stream, before its first launch) into `item_scratch`, a DEVICE buffer
  * of at least kvc_item_scratch_bytes(num_items) bytes, 16-byte aligned, from which the kernels read the items; the
  * kernels therefore see exactly the bytes that were checked.  (The item of a batch of one, except in a per-layer fit,
- * travels in the kernel arguments instead: the scratch is then checked but not written.)  Like every other buffer of an asynchronous call, the
- * host items (when they are in pinned memory) and the scratch belong to the call until its work on the stream is done:
- * calls that overlap in time need scratch buffers of their own.  kvc_apply and kvc_fit_state use the scratch; the
+ * travels in the kernel arguments instead: the scratch is then checked but not written, and a captured call keeps the
+ * item that it was captured with.)  Like every other buffer of an asynchronous call, the host items (when they are in
+ * pinned memory) and the scratch belong to the call until its work on the stream is done: calls that overlap in time
+ * need scratch buffers of their own.  kvc_apply and kvc_fit_state use the scratch; the
  * anchor calls take their one item by value and ignore it.  Tables are DEVICE int32 arrays [num_items][max_blocks] of
  * physical block ids; NULL means the identity mapping (contiguous rows). */
 typedef struct kvc_batch {

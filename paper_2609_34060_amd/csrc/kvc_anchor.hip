@@ -565,11 +565,11 @@ constexpr int kResChunk = kResWaves * kResTiles * 16;
 constexpr int kResDistChunk = kResWaves * kResDistTiles * 16;
 // The apply of a single chunk stages little per workgroup (16 KB of basis at head_dim 128) and is bound by memory, so
 // shorter workgroups, which balance better, cost it nothing: 2 tiles (256 tokens), and 8 with rotary keys, whose
-// workgroups form fp64 angles first.  One anchor of rank 32, 8 heads, us with 16 / 8 / 4 / 2 tiles: 4 layers x 1000 tokens
-// 20 / 20 / 13 / 10, 8 x 2048 36 / 28 / 28 / 31, 8 x 4096 70 / 72 / 72 / 71, 8 x 8192 145 / 144 / 135 / 132, 28 x 3328
-// 245 / 222 / 183 / 186, 32 x 4096 282 / 279 / 273 / 265; rotary 25 / 25 / 17 / 13, 44 / 32 / 33 / 40, 72 / 73 / 75 / 83,
-// 143 / 143 / 140 / 162, 246 / 228 / 191 / 222, 278 / 282 / 285 / 321.  (Ten chunks in registers at two waves per SIMD
-// took 69, 140, 234 and 272 us at the last four plain sizes.)
+// workgroups form fp64 angles first.  One anchor of rank 32, 8 heads, us with 16 / 8 / 4 / 2 tiles: 4 layers x 1000
+// tokens 20 / 20 / 13 / 10, 8 x 2048 36 / 28 / 28 / 31, 8 x 4096 70 / 72 / 72 / 71, 8 x 8192 145 / 144 / 135 / 132, 28
+// x 3328 245 / 222 / 183 / 186, 32 x 4096 282 / 279 / 273 / 265; rotary 25 / 25 / 17 / 13, 44 / 32 / 33 / 40, 72 / 73 /
+// 75 / 83, 143 / 143 / 140 / 162, 246 / 228 / 191 / 222, 278 / 282 / 285 / 321.  (Ten chunks in registers at two waves
+// per SIMD took 69, 140, 234 and 272 us at the last four plain sizes.)
 constexpr int res_apply_tiles(bool rope, int ncm) { return ncm > 1 ? kResTiles : rope ? 8 : 2; }
 int anchor_resident_chunk_tokens() { return kResDistChunk; }  // the shorter chunk (more partials)
 constexpr size_t kResMaxLds = 160 * 1024;
@@ -623,8 +623,8 @@ __device__ __forceinline__ int64_t lane_row_offset(const PoolView& pv, const Lan
 // Every chunk of unit `unit` into LDS: a thread takes (feature f, eight ranks of one chunk); the lanes of a wave
 // take 64 consecutive features, so each of the eight 4-byte loads is one coalesced 256-byte row segment.  A thread
 // always takes the same feature (kResThreads is a multiple of D).  ROPE with `rot`: each basis row is rotated like a
-// key row at position `pos` (B R(pos)^T), from the partner feature's values and one angle per thread.  NEG: negated (the
-// distances accumulate -A B onto the source row).
+// key row at position `pos` (B R(pos)^T), from the partner feature's values and one angle per thread.  NEG: negated
+// (the distances accumulate -A B onto the source row).
 template <int D, bool NEG, bool ROPE = false>
 __device__ __forceinline__ void stage_stacked(const AnchorArgs& a, int64_t unit, uint16_t* s_hi, uint16_t* s_lo,
                                               bool rot = false, double pos = 0.0) {
@@ -675,11 +675,12 @@ __device__ __forceinline__ void stage_stacked(const AnchorArgs& a, int64_t unit,
 // flight behind its arithmetic (before, a tile's loads were issued and waited for at once, or only after the previous
 // tile).  For that every load is unconditional (a branch around a load makes the compiler wait for more than it needs):
 // VEC (ranks multiples of 8, an anchor's coefficients of one unit within 4 GiB) reads clamped rows and ranks, whose
-// products meet zero basis rows or are masked where they would count, and chunks past the last one read it again.  Other
-// ranks take guarded element loads of the chunks that there are (8 layers x 8 heads x 4096 tokens, three anchors of rank
-// 12, gate / weights / apply: 178 / 773 / 219 us with every padding chunk loaded, 97 / 369 / 118 us without).  Their
-// values are packed, and so waited for, at once: the apply loads each chunk behind its products, the distances a whole
-// tile's chunks together (ten anchors of rank 20: apply 301 us behind each chunk and 335 together, weights 1494 and 1212).
+// products meet zero basis rows or are masked where they would count, and chunks past the last one read it again.
+// Other ranks take guarded element loads of the chunks that there are (8 layers x 8 heads x 4096 tokens, three anchors
+// of rank 12, gate / weights / apply: 178 / 773 / 219 us with every padding chunk loaded, 97 / 369 / 118 us without).
+// Their values are packed, and so waited for, at once: the apply loads each chunk behind its products, the distances a
+// whole tile's chunks together (ten anchors of rank 20: apply 301 us behind each chunk and 335 together, weights 1494
+// and 1212).
 template <bool VEC>
 __device__ __forceinline__ u32x4 load_chunk(const AnchorArgs& a, int c, int64_t unit, int t, int t_end, int g) {
   const int v = a.chunk_anchor[c], k0 = a.chunk_k0[c], r = a.rank[v];
@@ -761,8 +762,8 @@ __global__ __launch_bounds__(kResThreads) void apply_anchored_res_bf16(AnchorArg
   u32x4 raw[NQ], cw[NCM];
   float w[NCM];
   int64_t dof;
-  // the source row and the destination offset of tile j (a row whose source block id is out of range is neither read nor
-  // written); rows past the item read the last one and are not written
+  // the source row and the destination offset of tile j (a row whose source block id is out of range is neither read
+  // nor written); rows past the item read the last one and are not written
   auto load_row = [&](int j) __attribute__((always_inline)) {
     const int t = tile_t0(j) + n, tr = min(t, T - 1);
     const int64_t so = lane_row_offset(a.pv, lts, a.src_table, a.src_offset, tr, true, head);
@@ -867,9 +868,9 @@ __global__ __launch_bounds__(kResThreads) void apply_anchored_res_bf16(AnchorArg
 
 // Distances with every anchor of one head resident: a workgroup covers 1024 tokens of one (layer, K/V) and walks
 // the heads, staging each head's anchors once.  Per tile and anchor the accumulator starts from the source row in fp32
-// and takes -A_v B_v over the anchor's chunks (bf16 coefficients are exact MFMA operands, B as hi/lo); then its magnitudes
-// (weights) or squares (gate) are summed over the row.  ONE: every anchor has one chunk (ranks up to 32), so the source
-// row itself is the first product's addend.  Lane (g, n) keeps the sums of anchors v = 4u + g of its tiles'
+// and takes -A_v B_v over the anchor's chunks (bf16 coefficients are exact MFMA operands, B as hi/lo); then its
+// magnitudes (weights) or squares (gate) are summed over the row.  ONE: every anchor has one chunk (ranks up to 32), so
+// the source row itself is the first product's addend.  Lane (g, n) keeps the sums of anchors v = 4u + g of its tiles'
 // token n in registers across heads.
 // ROPE (weights): keys of a rotary cache are compared in canonical coordinates, R(-ps) C_src (the bases are canonical).
 // 32 layers x 8 heads x 4096 tokens, ten anchors of rank 32, before and with the rolling loads: weights 844 -> 648 us,
@@ -1108,11 +1109,11 @@ static bool res_vec(const AnchorArgs& a) {
 }
 
 // Chunk counts are rounded up to the instantiated 4, 7 and 10: a padding chunk costs its loads, which hit the cache.
-// Rank 32, 8 layers x 8 heads x 4096 tokens, us of gate / weights / apply so and with a count's own instantiation: 3 chunks
-// 48 / 184 / 95 and 48 / 184 / 93, 5 chunks 73 / 304 / 116 and 68 / 292 / 109, 8 chunks 147 / 592 / 168 and 146 / 581 /
-// 167, 9 chunks 129 / 479 / 168 and 120 / 497 / 165.  The apply, with the fewest instructions per chunk, has one for 2 as
-// well (4 layers, two chunks 49.8 us padded to 4 and 44.4; 1000 tokens 27.9 and 25.6), and one for a single chunk
-// (res_apply_tiles).
+// Rank 32, 8 layers x 8 heads x 4096 tokens, us of gate / weights / apply so and with a count's own instantiation: 3
+// chunks 48 / 184 / 95 and 48 / 184 / 93, 5 chunks 73 / 304 / 116 and 68 / 292 / 109, 8 chunks 147 / 592 / 168 and 146
+// / 581 / 167, 9 chunks 129 / 479 / 168 and 120 / 497 / 165.  The apply, with the fewest instructions per chunk, has
+// one for 2 as well (4 layers, two chunks 49.8 us padded to 4 and 44.4; 1000 tokens 27.9 and 25.6), and one for a
+// single chunk (res_apply_tiles).
 template <int D, bool GATE, bool ROPE>
 static hipError_t launch_dist_res(const AnchorArgs& a, dim3 grid, size_t lds, hipStream_t stream) {
   if (!res_vec(a))

@@ -99,8 +99,8 @@ kvc_status check_batch(const kvc_cache* c, const kvc_batch* b, bool needs_src) {
 }
 
 // The kernels read the items of a batch from the caller's device scratch; the library writes the checked host items
-// there on the call's stream before its first launch, so no unchecked item reaches a kernel.  The item of a batch of one
-// travels in the kernel arguments instead (not in a per-layer fit, whose kernels run for milliseconds).
+// there on the call's stream before its first launch, so no unchecked item reaches a kernel.  The item of a batch of
+// one travels in the kernel arguments instead (not in a per-layer fit, whose kernels run for milliseconds).
 bool in_arguments(const kvc_batch* b) { return b->num_items == 1; }
 
 kvc_status upload_items(const kvc_batch* b, hipStream_t stream) {
@@ -151,12 +151,12 @@ struct FitPlan {
   size_t units = 0, off_partials = 0, off_reflect = 0, off_beta = 0, off_vecs = 0, total = 0;
 };
 
-// Gram waves per fit launch: two rounds of a workgroup per CU for one item, whose ranges are equal; twice that for items
-// of different lengths, whose short last ranges leave CUs idle, as long as the ranges keep kGramLongRange tokens (below,
-// the partials outweigh it).  Whole fits of one layer x 8 heads at rank 32, us with half as many ranges and so (tokens in
-// a range): 64 requests 2570 and 2446 (1952), 1655 and 1610 (1056), 1377 and 1339 (832), 1106 and 1117 (512), 808 and 830
-// (288); 16 requests 1443 and 1380 (1120), 939 and 963 (640), 675 and 729 (416); 8 requests of two layers 1111 and 1081
-// (832), 988 and 976 (704), 910 and 904 (608); 64 requests with rotary keys 1890 and 1818 (832).
+// Gram waves per fit launch: two rounds of a workgroup per CU for one item, whose ranges are equal; twice that for
+// items of different lengths, whose short last ranges leave CUs idle, as long as the ranges keep kGramLongRange tokens
+// (below, the partials outweigh it).  Whole fits of one layer x 8 heads at rank 32, us with half as many ranges and so
+// (tokens in a range): 64 requests 2570 and 2446 (1952), 1655 and 1610 (1056), 1377 and 1339 (832), 1106 and 1117
+// (512), 808 and 830 (288); 16 requests 1443 and 1380 (1120), 939 and 963 (640), 675 and 729 (416); 8 requests of two
+// layers 1111 and 1081 (832), 988 and 976 (704), 910 and 904 (608); 64 requests with rotary keys 1890 and 1818 (832).
 constexpr int64_t kGramWaveTarget = 2048, kGramWaveTargetItems = 4096, kGramLongRange = 704;
 
 FitPlan plan_fit(const kvc_cache* c, const kvc_batch* b, int32_t lb, int32_t le) {

@@ -24,10 +24,10 @@ constexpr int kEigThreads = 512;
 constexpr int kEigWaves = kEigThreads / kWave;
 constexpr int kReflChunk = 16;  // reflectors staged in LDS per back-transformation chunk
 constexpr int kInvBatch = 32;   // eigenvectors per inverse-iteration batch (one lane each)
-// Inverse-iteration solves per eigenvector: with lambda within about 2^-24 of the spectrum's width, each solve
+// Inverse-iteration solves per eigenvector: with lambda within about 2^-28 of the spectrum's width, each solve
 // shrinks the other eigenvectors' components by that error over their gap, so two solves leave a residual far
-// below the fp32 rounding of the reduced matrix (about 1e-11 of the width in an fp64 simulation of the recurrence
-// on decaying and flat spectra).
+// below the fp32 rounding of the reduced matrix (about 1e-11 of the width already with lambda within 2^-24, in an fp64
+// simulation of the recurrence on decaying and flat spectra).
 constexpr int kInvSolves = 2;
 
 // fp64 cross-lane move by DPP (two 32-bit halves).  Lanes whose row is masked off keep an undefined value: the only
@@ -147,15 +147,15 @@ __device__ __forceinline__ void reflector_scalars(double x0, double s, double* o
 }
 
 // Number of eigenvalues of T below the shift x: sign changes of the leading minors p_i = (a_i - x) p_{i-1}
-// - b_{i-1}^2 p_{i-2} (two multiply-adds per step and shift, no division: the reciprocal of the ratio form costs several
-// times as much as the rest of its step).  T is scaled so that its norm is in [1, 2): |a_i - x| and b^2 stay below 8, so
-// eight steps grow the pair by less than 2^32, and with b^2 floored at 2^-120 (a perturbation of 2^-60 of the norm) eight
-// steps shrink it by 2^-480 at the most; every eight steps the pair is scaled by a power of two back to [1, 2), so
-// neither end of the range is reached.  A minor that comes out zero counts as positive, and the next one is then
-// -b^2 p_{i-2} with the opposite sign of p_{i-2}: one change over the two steps, whatever the sign before.  Each computed
-// count is exact for a T whose entries are off by a few 2^-53.  The signs are shifted into a word (one instruction a
-// step) and the changes counted every 32 steps.  512 units of N = 128, rank 16: bisection 54 us in the ratio form with
-// two shifts per lane, 17 us so.
+// - b_{i-1}^2 p_{i-2} (two multiply-adds per step and shift, no division: the reciprocal of the ratio form costs
+// several times as much as the rest of its step).  T is scaled so that its norm is in [1, 2): |a_i - x| and b^2 stay
+// below 8, so eight steps grow the pair by less than 2^32, and with b^2 floored at 2^-120 (a perturbation of 2^-60 of
+// the norm) eight steps shrink it by 2^-480 at the most; every eight steps the pair is scaled by a power of two back to
+// [1, 2), so neither end of the range is reached.  A minor that comes out zero counts as positive, and the next one is
+// then -b^2 p_{i-2} with the opposite sign of p_{i-2}: one change over the two steps, whatever the sign before.  Each
+// computed count is exact for a T whose entries are off by a few 2^-53.  The signs are shifted into a word (one
+// instruction a step) and the changes counted every 32 steps.  512 units of N = 128, rank 16: bisection 54 us in the
+// ratio form with two shifts per lane, 17 us so.
 template <int N>
 __device__ __forceinline__ int sturm_count(const double* sa, const double* sb2, double x) {
   double p0 = 0.0, p1 = 1.0;     // p_{i-2}, p_{i-1}
@@ -213,11 +213,11 @@ __device__ __forceinline__ int sturm_count(const double* sa, const double* sb2, 
 //
 // The matrix lives in registers as 16 x 16 fp32 tiles in the accumulator layout of v_mfma_f32_16x16x4_f32: tile wave W
 // of the kTriWaves (one per SIMD) holds the tile columns W, W + kTriWaves, ..  The rank-2 update of a tile is one such
-// MFMA (K slots 0 and 1 carry {v, w} against {-w, -v}, the other two zeros), and a wave's columns of A22 v are four FMAs
-// per tile, so nothing of the matrix goes through LDS and no row scalar is broadcast to a wave.  Tiles whose rows or
-// columns have all been reduced drop out (the loop over 16-row blocks is unrolled, the inner one is not).  p, K, w and
-// the scalars are computed in fp64, in one further wave, the chain wave, whose lanes own N / 64 columns each; v and w are
-// rounded to fp32 for the update, and the back-transformation uses the same fp32 v.
+// MFMA (K slots 0 and 1 carry {v, w} against {-w, -v}, the other two zeros), and a wave's columns of A22 v are four
+// FMAs per tile, so nothing of the matrix goes through LDS and no row scalar is broadcast to a wave.  Tiles whose rows
+// or columns have all been reduced drop out (the loop over 16-row blocks is unrolled, the inner one is not).  p, K, w
+// and the scalars are computed in fp64, in one further wave, the chain wave, whose lanes own N / 64 columns each; v and
+// w are rounded to fp32 for the update, and the back-transformation uses the same fp32 v.
 //
 // Step k, with three workgroup barriers (the other waves of the workgroup only meet them):
 //   chain   brings row k up to date with the pending update of step k - 1, forms the reflector and writes v;      [1]
@@ -225,11 +225,11 @@ __device__ __forceinline__ int sturm_count(const double* sa, const double* sb2, 
 //           four lane groups and row k + 1 (without step k's update) go to LDS;                                   [2]
 //   chain   sums the shares in a fixed order, forms K and w and writes {v, w};                                    [3]
 //   tiles   apply the update on the matrix cores, beside the chain's next reflector.
-// What bounds it is the serial chain of a step (two 64-lane fp64 sums, square root and reciprocal, three LDS round trips
-// and barriers).  With the chain computed by every tile wave instead (one barrier per step) the four waves of each of
-// the two units on a CU compete for the SIMDs with the same 200 instructions.  512 units of N = 128: 230 us with the
-// matrix in LDS (four waves sweeping its rows, the scalars broadcast from LDS), 152 us with register tiles and every
-// wave computing the chain, 122 us so; one unit of N = 64: 52, 39 and 35 us.
+// What bounds it is the serial chain of a step (two 64-lane fp64 sums, square root and reciprocal, three LDS round
+// trips and barriers).  With the chain computed by every tile wave instead (one barrier per step) the four waves of
+// each of the two units on a CU compete for the SIMDs with the same 200 instructions.  512 units of N = 128: 230 us
+// with the matrix in LDS (four waves sweeping its rows, the scalars broadcast from LDS), 152 us with register tiles and
+// every wave computing the chain, 122 us so; one unit of N = 64: 52, 39 and 35 us.
 constexpr int kTriWaves = 4;
 
 // LDS of the reduction: s_op [4][N] (v, w, 0, 0 of the pending update), s_vn [N] (v of the current step), share [4][N],
@@ -416,7 +416,7 @@ __device__ __forceinline__ void tri_reduce(const float* A, float* lds, double* s
 // registers; the padding spreads the 16 rows of a tile over the banks), the bisection's scaled T and counts (phase 3),
 // the inverse-iteration scratch fp64 [N][kInvBatch] x 2 (phase 4), X fp32 [r][N] (MGS, back-transformation); then
 // fp64 scalars and vectors; then the staging region: the reduction's vectors during phase 2, a chunk of reflectors
-// during phase 5.  81024 bytes for N = 128, so two units share a CU.
+// during phase 5.  78976 bytes for N = 128, so two units share a CU.
 template <int N>
 struct EigLds {
   static constexpr int kLda = N + 4;
@@ -431,6 +431,7 @@ struct EigLds {
   static constexpr size_t kReflStage = (size_t)kReflChunk * (N + 1) * 4;
   static constexpr size_t kStage = max2(kTri, kReflStage);
   static constexpr size_t kTotal = kMreg + kSmall + kStage;
+  static_assert(2 * kTotal <= 160 * 1024, "two units a CU");
 };
 
 // Four waves per SIMD (at most 128 VGPRs) so that two 512-thread units share a CU.
@@ -573,8 +574,9 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(4))
     {
       int rp = 1;
       while (rp < r) rp <<= 1;
-      // P lanes per eigenvalue, one shift each: the bracket is cut into S = P + 1 pieces per step: many lanes (few steps) while two units leave each SIMD a wave at the most, four from rank 17 on
-      // (P x steps is the work, and there it fills the SIMDs)
+      // P lanes per eigenvalue, one shift each, so a step cuts the bracket into S = P + 1 pieces: many lanes (few
+      // steps) while two units leave each SIMD a wave at the most, four from rank 17 on (P x steps is the work, and
+      // there it fills the SIMDs)
       const int plog = r <= 8 ? 5 : (r <= 16 ? 3 : 2), P = 1 << plog;
       static_assert(kEigThreads / KVC_MAX_RANK >= 4, "four lanes for every eigenvalue");
       const int S = P + 1;
@@ -738,11 +740,11 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(4))
     };
     // Clusters: runs of eigenvalues whose consecutive gaps are at most 1e-3 of the norm of T (the reorthogonalisation
     // criterion of LAPACK's inverse iteration, stein).  A vector is orthogonalised against the earlier vectors of its
-    // cluster only: the bisection's eigenvalues lie within about 2^-24 of the norm of T of the exact ones, so each
+    // cluster only: the bisection's eigenvalues lie within about 2^-28 of the norm of T of its own, so each
     // inverse-iteration solve scales a vector's components along eigenvectors at least 1e-3 away by at most
-    // 2^-24 / 1e-3 relative to its own, and the two solves leave vectors of different clusters orthogonal to about
-    // 4e-9 of the start's components.  The first vector of a cluster keeps the inverse iteration's normalisation.
-    // Bit j of the mask: vectors j and j + 1 share a cluster.
+    // 2^-28 / 1e-3 relative to its own, and the two solves leave vectors of different clusters orthogonal to about
+    // 1e-11 of the start's components, below the rounding of the stored vectors.  The first vector of a cluster keeps
+    // the inverse iteration's normalisation. Bit j of the mask: vectors j and j + 1 share a cluster.
     const double ctol = 1e-3 * tnorm;
     static_assert(KVC_MAX_RANK <= 2 * kWave, "two mask words");
     const uint64_t m0 = __ballot(lane + 1 < r && s_lam[lane] - s_lam[lane + 1] <= ctol);

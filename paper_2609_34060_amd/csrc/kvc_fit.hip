@@ -77,7 +77,8 @@ __device__ __forceinline__ void gram_all_tiles(f32x4* acc, const typename GramSe
   (gram_tile<D, Is, 0>(acc + Is, sh, sl), ...);
 }
 // A wave's partial: its accumulator fragments as they stand, 1 KB of consecutive lanes per tile (whole rows with both
-// mirrors took 288 scattered 4-byte stores per lane for head_dim 128; 8B/4K: 395 -> 264 us, serving layer 1809 -> 1609 us).
+// mirrors took 288 scattered 4-byte stores per lane for head_dim 128; 8B/4K: 395 -> 264 us, serving layer 1809 -> 1609
+// us).
 template <int D>
 __device__ __forceinline__ void gram_store_fragments(float* P, const f32x4* acc, int lane) {
 #pragma unroll
@@ -500,10 +501,10 @@ __device__ __forceinline__ void gram_f32_tiles(f32x4* acc, const float* z, std::
   (gram_f32_tile<D, Is>(acc, z), ...);
 }
 // One workgroup per partial: its four waves take the range's token batches in turn, each with every upper tile in
-// registers, and the four sums are added in a fixed order through LDS (tile fragments, 16 bytes per lane).  The next batch's rows are in flight while this one is multiplied.  Bound by the
-// fp32 matrix rate for head_dim 128 (36 tiles of 32 cycles per 4 tokens and wave), by latency for a few hundred
-// tokens (4 heads x 64, 256 tokens, two layers: 20 us against 70 us for fp32 FMAs on operands read from LDS, one
-// output entry per thread and two LDS reads per FMA).
+// registers, and the four sums are added in a fixed order through LDS (tile fragments, 16 bytes per lane).  The next
+// batch's rows are in flight while this one is multiplied.  Bound by the fp32 matrix rate for head_dim 128 (36 tiles of
+// 32 cycles per 4 tokens and wave), by latency for a few hundred tokens (4 heads x 64, 256 tokens, two layers: 20 us
+// against 70 us for fp32 FMAs on operands read from LDS, one output entry per thread and two LDS reads per FMA).
 template <int D>
 struct GramF32 {
   static constexpr int FT = D / 16, NT = gram_tiles(D);

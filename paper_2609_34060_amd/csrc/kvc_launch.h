@@ -48,9 +48,9 @@ inline dim3 chunk_grid(int chunks, int units, int item_layers, int32_t order) {
 // Item of a launch.  One item travels in the kernel arguments (no copy to the device ahead of the first kernel: that
 // copy and the gap after it cost about as much as a small apply).  item_ptr: Args is the kernel's first parameter, so
 // `one` lies at its own offset in the argument segment, and both places are read by scalar loads through one
-// constant-space pointer (a copy by value cost the apply of 64 requests 1-5 % in registers).  item_of: by value, for the
-// fit's kernels (with the constant-space pointer the compiler keeps the projection's LDS fragments in registers, 179
-// instead of 128).
+// constant-space pointer (a copy by value cost the apply of 64 requests 1-5 % in registers).  item_of: by value, for
+// the fit's kernels (with the constant-space pointer the compiler keeps the projection's LDS fragments in registers,
+// 179 instead of 128).
 typedef const __attribute__((address_space(4))) kvc_item* ItemPtr;
 template <class Args>
 __device__ __forceinline__ ItemPtr item_ptr(const Args& a, int i) {

@@ -164,8 +164,8 @@ def _stream_handle(stream) -> ctypes.c_void_p:
 
 
 # The library copies the host items (pinned memory) of a batch of several into its device scratch on the call's stream,
-# so the copy reads the host bytes only when the stream reaches it, and the kernels read the batch's tables and states.  A
-# Batch passed as a temporary would be freed on return and its pinned block handed to the next allocation before that;
+# so the copy reads the host bytes only when the stream reaches it, and the kernels read the batch's tables and states.
+# A Batch passed as a temporary would be freed on return and its pinned block handed to the next allocation before that;
 # calls that use a batch's items therefore keep it alive until an event recorded after the call has completed.  A
 # stream's events complete in order, so each call looks at the oldest ones only (of every stream), and a completed event
 # serves again: a call that queried every event in flight and made a new one spent more host time the more were queued.
