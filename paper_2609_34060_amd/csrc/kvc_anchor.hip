@@ -724,7 +724,7 @@ __device__ __forceinline__ void row_f32(const u32x4* raw, f32x4* x) {
 // rounding.
 // ROPE: keys of a rotary cache, C_dst = R(pd - ps) C_src + sum_v w_v A_v (B_v R(pd)^T) (bases staged rotated, the
 // source rotated in the accumulator; rows past T_s get the rotated source).
-// 32 layers x 8 heads x 4096 tokens, ten anchors of rank 32: 680 us before the rolling loads, 649 us with them.
+// 32 layers x 8 heads x 4096 tokens, ten anchors of rank 32: 668 us before the rolling loads, 626 us with them.
 template <int D, bool ROPE, int NCM, bool VEC>
 __global__ __launch_bounds__(kResThreads) void apply_anchored_res_bf16(AnchorArgs a) {
   constexpr int MT = D / 16, NQ = D / 32, TPW = res_apply_tiles(ROPE, NCM);
@@ -873,8 +873,8 @@ __global__ __launch_bounds__(kResThreads) void apply_anchored_res_bf16(AnchorArg
 // the source row itself is the first product's addend.  Lane (g, n) keeps the sums of anchors v = 4u + g of its tiles'
 // token n in registers across heads.
 // ROPE (weights): keys of a rotary cache are compared in canonical coordinates, R(-ps) C_src (the bases are canonical).
-// 32 layers x 8 heads x 4096 tokens, ten anchors of rank 32, before and with the rolling loads: weights 844 -> 648 us,
-// gate 470 -> 375 us; four anchors of rank 16: 509 -> 339 and 260 -> 177 us, apply 548 -> 324 us.
+// 32 layers x 8 heads x 4096 tokens, ten anchors of rank 32, before and with the rolling loads: weights 832 -> 603 us,
+// gate 436 -> 320 us; four anchors of rank 16: 496 -> 315 and 239 -> 153 us, apply 549 -> 321 us.
 template <int D, bool GATE, bool ROPE, int NCM, bool VEC, bool ONE>
 __global__ __launch_bounds__(kResThreads) void anchor_dist_res_bf16(AnchorArgs a) {
   constexpr int MT = D / 16, NQ = D / 32, TPW = GATE ? kResTiles : kResDistTiles;
