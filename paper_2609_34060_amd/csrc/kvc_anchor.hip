@@ -680,7 +680,8 @@ __device__ __forceinline__ void stage_stacked(const AnchorArgs& a, int64_t unit,
 // of rank 12, gate / weights / apply: 178 / 773 / 219 us with every padding chunk loaded, 97 / 369 / 118 us without).
 // Their values are packed, and so waited for, at once: the apply loads each chunk behind its products, the distances a
 // whole tile's chunks together (ten anchors of rank 20: apply 301 us behind each chunk and 335 together, weights 1494
-// and 1212).
+// and 1212), and neither loads anything behind a wave's last tile (28 layers x 8 heads x 130 tokens, eight anchors of
+// rank 28, gate and apply: 41 and 67 us with those loads, 33 and 54 without).
 template <bool VEC>
 __device__ __forceinline__ u32x4 load_chunk(const AnchorArgs& a, int c, int64_t unit, int t, int t_end, int g) {
   const int v = a.chunk_anchor[c], k0 = a.chunk_k0[c], r = a.rank[v];
@@ -830,7 +831,7 @@ __global__ __launch_bounds__(kResThreads) void apply_anchored_res_bf16(AnchorArg
           for (int e = 0; e < 4; ++e) acc[mt][e] = fmaf(wc, p[e], acc[mt][e]);
         }
       }
-      if (VEC || c < NC) load_c(jn, c);
+      if (VEC || (c < NC && j + 1 < nt)) load_c(jn, c);
     }
     if (tile_t0(j) + 16 > Ts) {  // uniform: the tile where the coverage ends
       // rows past T_s: the rotated source with a shift, else bit copies
@@ -991,7 +992,7 @@ __global__ __launch_bounds__(kResThreads) void anchor_dist_res_bf16(AnchorArgs a
         }
         if (VEC) cw[c] = load_chunk<VEC>(a, c, unit_n, tile_t0(jn) + n, Tl, g);
       }
-      if (!VEC)
+      if (!VEC && (!last || h + 1 < h_hi))
 #pragma unroll
         for (int c = 0; c < NCM; ++c)
           if (c < NC) cw[c] = load_chunk<VEC>(a, c, unit_n, tile_t0(jn) + n, Tl, g);

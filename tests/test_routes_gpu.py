@@ -25,7 +25,18 @@ def _pools(L, H, d, bs, blocks, dtype, seed):
     (128, (64, 32)), (128, (40, 96, 8)), (128, (64,) * 5), (128, (5, 32, 17)), (64, (33, 64, 1)), (128, (12,) * 9),
     (128, (24, 8)), (64, (64,)), (128, (3,)), (64, (7, 2, 20)), (128, (20,) * 10)])
 def test_resident_anchor_chunk_counts(d, ranks):
-    L, H, T, Ts, bs = 1, 2, 1201, 1187, 16
+    _check_resident(d, ranks, 1201, 1187)
+
+
+# Waves with no tile, one tile and two tiles of 16 tokens (eight waves take a segment's tiles in turn).
+@pytest.mark.parametrize("d,ranks,T,Ts", [
+    (128, (28,) * 8, 130, 130), (64, (10, 39), 7, 5), (128, (12,), 113, 96), (128, (32,) * 10, 130, 120), (64, (8,), 16, 1)])
+def test_resident_anchor_short_segments(d, ranks, T, Ts):
+    _check_resident(d, ranks, T, Ts)
+
+
+def _check_resident(d, ranks, T, Ts):
+    L, H, bs = 1, 2, 16
     need = -(-(T + 5) // bs)
     pool, ids, g = _pools(L, H, d, bs, 2 * need, torch.bfloat16, sum(ranks) + d)
     tab = (ids[:need], ids[need:])
